@@ -21,9 +21,6 @@ struct PtcGeo {
 // items are staged in LDS one at a time.
 struct PtcLayerDev {
   int cin, cout;
-  int chunk_ch;    // input channels per weight-gradient chunk
-  int nchunk;      // weight-gradient chunks
-  int kchunk;      // real K per weight-gradient chunk (72 * chunk_ch padded to 32)
   int fw_items;    // forward items 9 * Cin
   int fw_ks;       // forward 32-deep K steps (fw_items padded to 4, / 4)
   int fw_ipc;      // forward items per LDS chunk (multiple of 4, at most 16)
@@ -39,9 +36,6 @@ inline PtcLayerDev ptc_layer_desc(int cin, int cout) {
   PtcLayerDev L{};
   L.cin = cin;
   L.cout = cout;
-  L.chunk_ch = cin < 4 ? cin : 4;
-  L.nchunk = (cin + L.chunk_ch - 1) / L.chunk_ch;
-  L.kchunk = ((72 * L.chunk_ch + 31) / 32) * 32;
   L.fw_items = 9 * cin;
   L.fw_ks = (L.fw_items + 3) / 4;
   L.fw_ipc = 4 * L.fw_ks < 16 ? 4 * L.fw_ks : 16;
@@ -67,13 +61,16 @@ hipError_t launch_ptc_forward(const PtcGeo &q, const PtcLayerDev &L, const int *
                               int out_f32, int par, int variant, int zero_par, hipStream_t st);
 // layer-0 activations from an FP32 packed even field
 hipError_t launch_ptc_input(int64_t vh, const void *in_even, void *act, hipStream_t st);
-hipError_t launch_ptc_bwd_data(const PtcGeo &q, const PtcLayerDev &L, const float *delta, float *gy, int par,
-                               hipStream_t st);
-hipError_t launch_ptc_adjoint_gather(const PtcGeo &q, int cin, const float *gy, float *gpsi, int par, hipStream_t st);
-hipError_t launch_ptc_bwd_weight(const PtcGeo &q, const PtcLayerDev &L, const void *in, const float *delta,
-                                 float *partial, int par, int groups, hipStream_t st);
-hipError_t launch_ptc_weight_reduce(const PtcLayerDev &L, const float *partial, int groups, float *gw, int accumulate,
-                                    hipStream_t st);
+// the output cotangent (FP32 packed even spinor) as the BF16 delta of the last layer
+hipError_t launch_ptc_delta(int64_t vh, const float *in_even, void *delta, hipStream_t st);
+// delta, gpsi: BF16 cotangents of the layer's output and input; zero_par:
+// parity on which delta vanishes (not read there), -1: none
+hipError_t launch_ptc_bwd_data(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *delta, void *gpsi,
+                               int zero_par, hipStream_t st);
+// weight gradient of the layer into gw; partial: ptc_weight_partial_bytes
+size_t ptc_weight_partial_bytes(const PtcLayerDev &L, size_t vh, int zero_par);
+hipError_t launch_ptc_bwd_weight(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *in,
+                                 const void *delta, float *partial, float *gw, int zero_par, hipStream_t st);
 hipError_t launch_ptc_pack(const PtcLayerDev &L, const float *W, hipStream_t st);
 hipError_t launch_adam(float *w, float *m, float *v, const float *g, size_t n, float lr, float b1, float b2, float eps,
                        float bc1, float bc2, float gscale, hipStream_t st);

@@ -19,6 +19,7 @@
 // input channels in LDS (parallel transport, converted to BF16), then each of
 // its 4 waves runs the MFMA tiles it owns; weights come pre-packed in the
 // per-lane A-operand order, so each A fragment is one coalesced 16-byte load.
+#include <algorithm>
 #include <type_traits>
 
 #include "lqcd_internal.h"
@@ -48,64 +49,6 @@ __device__ __forceinline__ void act_load(const bf16 *__restrict__ blk, int64_t v
 
 __device__ __forceinline__ f32x4_t mfma_bf16(const bf16x8_t &a, const bf16x8_t &b, const f32x4_t &c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// (T_p psi)(x) for one channel of a channel-interleaved activation field.
-// x: site index of parity `par`; the identity path reads parity par, the hops
-// read parity 1 - par. Boundary phases as in the Dirac operator.
-template <int RECON>
-__device__ __forceinline__ void transport_one(const PtcGeo &q, const bf16 *__restrict__ act, int C, int ch, int p,
-                                              const Site &x, int s, cpx<float> (&out)[4][3]) {
-  const int par = x.p;
-  const int64_t vh = q.g.Vh, vs = vh * C;
-  const bf16 *blk_same = act + (int64_t)par * vs * 24;
-  const bf16 *blk_other = act + (int64_t)(1 - par) * vs * 24;
-  float r[24];
-  if (p == 0) {
-    act_load(blk_same, vs, (int64_t)s * C + ch, r);
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) out[sp][c] = mk<float>(r[6 * sp + 2 * c], r[6 * sp + 2 * c + 1]);
-    return;
-  }
-  const int mu = (p - 1) >> 1;
-  const bool fwd = ((p - 1) & 1) == 0;
-  int w = 0, n = 0;
-  switch (mu) {
-    case 0: n = hop<0>(q.g, x, fwd ? 1 : -1, &w); break;
-    case 1: n = hop<1>(q.g, x, fwd ? 1 : -1, &w); break;
-    case 2: n = hop<2>(q.g, x, fwd ? 1 : -1, &w); break;
-    default: n = hop<3>(q.g, x, fwd ? 1 : -1, &w); break;
-  }
-  act_load(blk_other, vs, (int64_t)n * C + ch, r);
-  float lv[RECON];
-  if (fwd)
-    load_site<float, RECON, float>(q.gauge + (int64_t)(2 * mu + par) * vh * RECON, vh, s, lv);
-  else
-    load_site<float, RECON, float>(q.gauge + (int64_t)(2 * mu + 1 - par) * vh * RECON, vh, n, lv);
-  const Link<float> U0 = unpack_link<RECON, float>(lv);
-  const float ph = (mu == 3 && (w & 1) && q.g.bc_t < 0) ? -1.f : 1.f;
-  Link<float> U;  // U or U^+, times the boundary sign
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) U.m[a][b] = ph * (fwd ? U0.m[a][b] : conj(U0.m[b][a]));
-#pragma unroll
-  for (int sp = 0; sp < 4; ++sp) {
-    cpx<float> v[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = mk<float>(r[6 * sp + 2 * c], r[6 * sp + 2 * c + 1]);
-    su3_mv(U, v, out[sp]);
-  }
-}
-
-__device__ __forceinline__ void transport_any(const PtcGeo &q, const bf16 *act, int C, int ch, int p, const Site &x,
-                                              int s, cpx<float> (&out)[4][3]) {
-  if (q.recon == 12)
-    transport_one<12>(q, act, C, ch, p, x, s, out);
-  else
-    transport_one<18>(q, act, C, ch, p, x, s, out);
 }
 
 // Neighbour table of the transport paths: entry [par][p-1][s] (p = 1..8) is
@@ -630,253 +573,421 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
 }
 
 // ---------------------------------------------------------------------------
-// backward, data: gY[(i,p)](x) = sum_o W[o,i,p]^+ delta_o(x), on parity par.
-// Output channel-interleaved with Cin*9 channels.
+// backward pass. The cotangents delta between layers are held as the BF16
+// operands both GEMMs take them as (each reader of an FP32 field would round
+// it first), per site [colour][channel][spin][re/im]: a 16-byte piece is the 8
+// K values of one channel and colour in the B operand of a 16x16x32 product.
 
-__global__ void __launch_bounds__(kPtcThreads) ptc_bwd_data_kernel(PtcGeo q, PtcLayerDev L, const float *delta,
-                                                                    float *gy, int par) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int krow = L.kadj + kLdsPad;
-  __bf16 *Bt = reinterpret_cast<__bf16 *>(smem);  // [48][krow]: delta, k = 2*(o*4+s) + r
-  const int s0 = xcd_remap(blockIdx.x, gridDim.x) * kTile;
+// (colour c of channel o is ch pieces after colour c - 1)
+__device__ __forceinline__ const uint4 *delta_at(const bf16 *delta, int64_t vh, int ch, int par, int s, int o) {
+  return reinterpret_cast<const uint4 *>(delta) + ((int64_t)par * vh + s) * 3 * ch + o;
+}
+
+// The output cotangent (FP32 packed even spinor, one channel) in that layout.
+__global__ void __launch_bounds__(256) ptc_delta_kernel(int64_t vh, const float *in_even, bf16 *delta) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= vh) return;
+  float r[24];
+  load_spinor_reals<float, 24, float>(in_even, vh, s, r);
+  uint4 *d = reinterpret_cast<uint4 *>(delta) + 3 * s;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    bf16x8_t v;
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp) {
+      v[2 * sp] = (__bf16)r[6 * sp + 2 * c];
+      v[2 * sp + 1] = (__bf16)r[6 * sp + 2 * c + 1];
+    }
+    d[c] = __builtin_bit_cast(uint4, v);
+  }
+}
+
+// Data: gpsi_i(x) = sum_p T_p^+ (sum_o W[o,i,p]^+ delta_o)(x), T_{+mu}^+ = T_{-mu}.
+// The adjoint product is taken at the site T_p^+ reads from and transported in
+// registers: in the 16x16 result tiles a lane holds the same site and rows for
+// each of the three colours (one tile per colour), so the SU(3) product of a
+// (channel, spin) vector mixes registers of one lane, in FP32, and the 9 paths
+// are summed in FP32 accumulators. Nothing but delta is read and gpsi written:
+// the form with the 9 Cin intermediate fields in memory (13.8 KB per site at 16
+// channels, written and read in FP32) was bound by them.
+// A wave owns 16 sites; the weights of a path (32 KB at 16 -> 16) are staged in
+// LDS for the workgroup's 64 sites, and the cotangents, link and weights of hop
+// p + 1 are loaded before hop p is multiplied: one wave per SIMD with the
+// registers of both (two waves of half the rows each spill). The loads of the
+// hop loop are unconditional (the last one repeats hop 8) and the tile counts
+// compile-time: a branch around a prefetch makes the compiler wait for all
+// outstanding loads where the paths join.
+// MT m-tiles (16 rows, 2 input channels each) and KS K steps (4 output
+// channels each), both rounded up from the layer's.
+// zero_par: parity on which delta vanishes (the output cotangent lives on even
+// sites), -1: none.
+constexpr int kBwSites = 64;
+constexpr int kBwThreads = 256;
+
+template <int RC, int KS> struct BwPath {
+  bf16x8_t b[KS][3];
+  float lv[RC];
+  float ph;
+};
+
+template <int RC, int MT, int KS>
+__global__ void __launch_bounds__(kBwThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
+ptc_bwd_data_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, const bf16 *__restrict__ delta,
+                    bf16 *__restrict__ gpsi, int zero_par) {
+  constexpr int NFRAG = MT * KS * 64, PER = (NFRAG + kBwThreads - 1) / kBwThreads;
+  __shared__ bf16x8_t As[2][NFRAG];
+  const int wl0 = xcd_remap(blockIdx.x, gridDim.x);
+  const int par = wl0 & 1, s0 = (wl0 >> 1) * kBwSites;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int e = threadIdx.x; e < 48 * krow; e += kPtcThreads) Bt[e] = (__bf16)0.f;
-  __syncthreads();
-  const int64_t vsd = (int64_t)q.g.Vh * L.cout;
-  const float *dblk = delta + (int64_t)par * vsd * 24;
-  for (int it = threadIdx.x; it < kTile * L.cout; it += kPtcThreads) {
-    const int sl = it / L.cout, o = it % L.cout;
-    const int s = s0 + sl;
-    float r[24];
-    if (s < q.g.Vh)
-      load_spinor_reals<float, 24, float>(dblk, vsd, (int64_t)s * L.cout + o, r);
-    else
-      for (int k = 0; k < 24; ++k) r[k] = 0.f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      bf16x8_t v;
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp) {
-        v[2 * sp] = (__bf16)r[6 * sp + 2 * c];
-        v[2 * sp + 1] = (__bf16)r[6 * sp + 2 * c + 1];
-      }
-      *reinterpret_cast<bf16x8_t *>(Bt + (c * kTile + sl) * krow + 8 * o) = v;
-    }
-  }
-  __syncthreads();
-  const int C9 = L.cin * 9;
-  const int64_t vsg = (int64_t)q.g.Vh * C9;
-  float *gblk = gy + (int64_t)par * vsg * 24;
-  const int ks_n = L.kadj / 32;
-  const int ntile_total = L.madj_tiles * 3;
-  for (int tid = wave; tid < ntile_total; tid += 4) {
-    const int mt = tid / 3, nt = tid % 3;
-    f32x4_t acc = {0, 0, 0, 0};
-    for (int ks = 0; ks < ks_n; ++ks) {
-      const bf16x8_t a = ((const bf16x8_t *)L.Aadj)[((size_t)mt * ks_n + ks) * 64 + lane];
-      const bf16x8_t b = lds_frag(Bt + (nt * kTile + (lane & 15)) * krow + ks * 32 + 8 * (lane >> 4));
-      acc = mfma_bf16(a, b, acc);
-    }
-    const int sl = lane & 15, s = s0 + sl;
-    if (s >= q.g.Vh) continue;
-    // rows 4*(lane>>4)+j: two complex entries (k', k'+1) of the same (i,p) group
-#pragma unroll
-    for (int j = 0; j < 4; j += 2) {
-      const int m = mt * 16 + 4 * (lane >> 4) + j;
-      const int kp = m >> 1;  // (i*9 + p)*4 + s'
-      const int ip = kp >> 2, sp = kp & 3;
-      if (ip < C9) {
-        float *dst = gblk + ((int64_t)(sp * 6 + nt * 2) / 4 * vsg + (int64_t)s * C9 + ip) * 4 + ((sp * 6 + nt * 2) & 3);
-        dst[0] = acc[j];
-        dst[1] = acc[j + 1];
-      }
-    }
-  }
-}
+  const int g = lane >> 4;
+  const int64_t vh = q.g.Vh;
+  const int s_own = s0 + 16 * wave + (lane & 15);
+  const bool valid = s_own < vh;
+  const int s = valid ? s_own : 0;
+  const int nks = L.kadj / 32, rows = 8 * L.cin;
+  const bf16x8_t *A = (const bf16x8_t *)L.Aadj;
 
-// gpsi_i(x) = sum_p (T_p^+ gY[i,p])(x); T_{+mu}^+ = T_{-mu}. One thread per
-// (site, channel) of parity par.
-__global__ void __launch_bounds__(256) ptc_adjoint_gather_kernel(PtcGeo q, int cin, const float *gy, float *gpsi,
-                                                                  int par) {
-  const int pidx = xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (pidx >= q.g.Vh * cin) return;
-  const int s = pidx / cin, i = pidx - s * cin;
-  const Site x = decode_site(q.g, s, par);
-  const int C9 = cin * 9;
-  const int64_t vh = q.g.Vh, vsg = vh * C9;
-  const float *same = gy + (int64_t)par * vsg * 24;
-  const float *other = gy + (int64_t)(1 - par) * vsg * 24;
-  float acc[24], r[24];
-  load_spinor_reals<float, 24, float>(same, vsg, (int64_t)s * C9 + i * 9 + 0, acc);
-  for (int mu = 0; mu < 4; ++mu) {
-    for (int f = 0; f < 2; ++f) {
-      // f = 0: term T_{-mu} gY[i,+mu] = U_mu(x-mu)^+ g(x-mu); f = 1: T_{+mu} gY[i,-mu] = U_mu(x) g(x+mu)
-      const int p = f == 0 ? 1 + 2 * mu : 2 + 2 * mu;
-      int w = 0, n = 0;
-      const int step = f == 0 ? -1 : 1;
-      switch (mu) {
-        case 0: n = hop<0>(q.g, x, step, &w); break;
-        case 1: n = hop<1>(q.g, x, step, &w); break;
-        case 2: n = hop<2>(q.g, x, step, &w); break;
-        default: n = hop<3>(q.g, x, step, &w); break;
-      }
-      load_spinor_reals<float, 24, float>(other, vsg, (int64_t)n * C9 + i * 9 + p, r);
-      float lv[18];
-      Link<float> U;
-      if (q.recon == 12) {
-        if (f == 0)
-          load_site<float, 12, float>(q.gauge + (int64_t)(2 * mu + 1 - par) * vh * 12, vh, n, lv);
-        else
-          load_site<float, 12, float>(q.gauge + (int64_t)(2 * mu + par) * vh * 12, vh, s, lv);
-        U = unpack_link<12, float>(lv);
-      } else {
-        if (f == 0)
-          load_site<float, 18, float>(q.gauge + (int64_t)(2 * mu + 1 - par) * vh * 18, vh, n, lv);
-        else
-          load_site<float, 18, float>(q.gauge + (int64_t)(2 * mu + par) * vh * 18, vh, s, lv);
-        U = unpack_link<18, float>(lv);
-      }
-      const float ph = (mu == 3 && (w & 1) && q.g.bc_t < 0) ? -1.f : 1.f;
-      for (int sp = 0; sp < 4; ++sp) {
-        cpx<float> v[3], u[3];
-        for (int c = 0; c < 3; ++c) v[c] = mk<float>(r[6 * sp + 2 * c], r[6 * sp + 2 * c + 1]);
-        if (f == 0)
-          su3_adj_mv(U, v, u);
-        else
-          su3_mv(U, v, u);
-        for (int c = 0; c < 3; ++c) {
-          acc[6 * sp + 2 * c] += ph * u[c].re;
-          acc[6 * sp + 2 * c + 1] += ph * u[c].im;
+  f32x4_t acc[MT][3];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[t][c] = f32x4_t{0, 0, 0, 0};
+
+  // channels beyond Cout meet zero weights: those lanes load channel 0
+  auto fetch_delta = [&](bf16x8_t (&b)[KS][3], int np, int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int o = 4 * ks + g;
+      const uint4 *d = delta_at(delta, vh, L.cout, np, n, o < L.cout ? o : 0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) b[ks][c] = __builtin_bit_cast(bf16x8_t, d[c * L.cout]);
+    }
+  };
+  // T_p^+ reads the site that path p' reaches, p' the opposite hop (entry of path p)
+  auto entry = [&](int p) { return nbr[((int64_t)par * 8 + ((p - 1) ^ 1)) * vh + s]; };
+  auto fetch = [&](BwPath<RC, KS> &f, int p, int e) __attribute__((always_inline)) {
+    const int n = e & 0x7fffffff, mu = (p - 1) >> 1;
+    const bool at_n = ((p - 1) & 1) == 0;  // U_mu(x - mu)^+ from x - mu, else U_mu(x) from x + mu
+    f.ph = e < 0 ? -1.f : 1.f;
+    load_site<float, RC, float>(q.gauge + (int64_t)(2 * mu + (at_n ? 1 - par : par)) * vh * RC, vh, at_n ? n : s,
+                                f.lv);
+    fetch_delta(f.b, 1 - par, n);
+  };
+  // fragments of path p: rows p rows .. + 16 MT (a tile may run into the next
+  // path's rows, whose results are unused; beyond the last row it is clamped)
+  bf16x8_t ap[PER];
+  auto load_a = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int e = threadIdx.x + k * kBwThreads;
+      const int ln = e & 63, t = (e >> 6) / KS, ks = (e >> 6) % KS;
+      const int r = p * rows + 16 * t + (ln & 15), rt = min(r >> 4, L.madj_tiles - 1);
+      ap[k] = A[((size_t)rt * nks + min(ks, nks - 1)) * 64 + ((ln & 48) | (r & 15))];
+    }
+  };
+  auto store_a = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int e = threadIdx.x + k * kBwThreads;
+      // K steps beyond the layer's are zero (masked without a branch)
+      uint4 w = __builtin_bit_cast(uint4, ap[k]);
+      const uint32_t keep = (e >> 6) % KS < nks ? ~0u : 0u;
+      w = make_uint4(w.x & keep, w.y & keep, w.z & keep, w.w & keep);
+      if (NFRAG % kBwThreads == 0 || e < NFRAG) As[buf][e] = __builtin_bit_cast(bf16x8_t, w);
+    }
+  };
+  // one path's product W_p^+ delta for m-tile t
+  auto product = [&](const bf16x8_t (&b)[KS][3], int buf, int t, f32x4_t (&C)[3]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) C[c] = f32x4_t{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8_t a = As[buf][(t * KS + ks) * 64 + lane];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) C[c] = mfma_bf16(a, b[ks][c], C[c]);
+    }
+  };
+  if (zero_par != par) {  // identity path
+    bf16x8_t b[KS][3];
+    load_a(0);
+    fetch_delta(b, par, s);
+    store_a(0);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < MT; ++t) product(b, 0, t, acc[t]);
+  }
+  if (zero_par != 1 - par) {  // hops: weights of hop p in buffer p % 2
+    BwPath<RC, KS> fa, fb;
+    int e1 = entry(1);
+    load_a(1);
+    fetch(fa, 1, e1);
+    e1 = entry(2);
+    store_a(1);
+    auto step = [&](auto at_n, const BwPath<RC, KS> &f, BwPath<RC, KS> &next, int p) __attribute__((always_inline)) {
+      __syncthreads();  // hop p is in LDS, hop p - 1 has been multiplied
+      const int pn = min(p + 1, 8), e = e1;
+      load_a(pn);
+      fetch(next, pn, e);
+      e1 = entry(min(p + 2, 8));
+      __builtin_amdgcn_sched_barrier(0);
+      const Link<float> U = unpack_link<RC, float>(f.lv);
+      // the matrix products of tile t + 1 run beside the transport of tile t;
+      // the barriers keep the compiler from opening more tiles (it spills)
+      f32x4_t C[2][3];
+      product(f.b, p & 1, 0, C[0]);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < MT) product(f.b, p & 1, t + 1, C[(t + 1) & 1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          cpx<float> v[3], u[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) v[c] = mk<float>(C[t & 1][c][2 * h], C[t & 1][c][2 * h + 1]);
+          if constexpr (at_n.value)
+            su3_adj_mv(U, v, u);
+          else
+            su3_mv(U, v, u);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            acc[t][c][2 * h] += f.ph * u[c].re;
+            acc[t][c][2 * h + 1] += f.ph * u[c].im;
+          }
         }
+        // (the sums are formed here: left alone they are sunk to the end of the
+        // hop loop, with the products of all tiles held in registers until then)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) __asm__ volatile("" : "+v"(acc[t][c]));
       }
+      __builtin_amdgcn_sched_barrier(0);
+      store_a((p + 1) & 1);
+    };
+#pragma unroll 1
+    for (int p = 1; p < 9; p += 2) {
+      step(std::true_type(), fa, fb, p);
+      step(std::false_type(), fb, fa, p + 1);
     }
   }
-  store_spinor_reals<float, 24, float>(gpsi + (int64_t)par * vh * cin * 24, vh * cin, pidx, acc);
+  if (!valid) return;
+  // row 16 t + 4 g + jj: channel 2 t + g / 2, spin 2 (g % 2) + jj / 2, part jj % 2
+  uint2 *out = reinterpret_cast<uint2 *>(gpsi) + ((int64_t)par * vh + s) * 6 * L.cin;
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int i = 2 * t + (g >> 1);
+    if (i >= L.cin) continue;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      out[2 * (c * L.cin + i) + (g & 1)] =
+          make_uint2(__builtin_bit_cast(uint32_t, pack_bf16x2(acc[t][c][0], acc[t][c][1])),
+                     __builtin_bit_cast(uint32_t, pack_bf16x2(acc[t][c][2], acc[t][c][3])));
+  }
 }
 
-// ---------------------------------------------------------------------------
-// backward, weights: partial sums over site tiles of
+// Weights: partial sums over site tiles of
 //   G[(m', r)][k'] = sum_{(n, r')} D[(m', r)][(n, r')] Y'[(n, r')][k'],
 //   D = [[dr, di],[di, -dr]],  Y' = (Yr, Yi),
-// i.e. G = (Re, Im) of sum_x delta (T psi)^+. A workgroup owns one input
-// channel chunk and a strided set of site tiles of parity par.
+// i.e. G = (Re, Im) of sum_x delta (T psi)^+. A workgroup owns a chunk of 16
+// items (q = p Cin + i: with 16 channels one path) and a contiguous range of
+// tiles of 16 sites; thread (site, item) transports one channel in FP32 and writes it
+// as BF16 to LDS, row (item, spin), K = (colour, site, re/im); delta is staged
+// the same way (row (channel, spin); the rows r = 1 are formed from the words
+// on reading). The next tile's loads are issued before the products. The
+// PATH: 16 input channels, chunk = path (uniform over the workgroup); JW: m-tiles
+// per wave (the layer's halved and rounded up; rows beyond Cout are unused). The
+// transports bound it (about 350 vector instructions per wave and tile against
+// 24 matrix instructions): 172 us for a 16 -> 16 layer at 16^4 with the sum over
+// groups; 942 us when a workgroup took 4 channels with all 9 paths, one parity,
+// and wrote its operands to LDS in 2-byte pieces.
+constexpr int kWgThreads = 256;
+constexpr int kWgRow = 2 * 3 * kTile + kLdsPad;  // bf16 per LDS row
 
-__global__ void __launch_bounds__(kPtcThreads) ptc_bwd_weight_kernel(PtcGeo q, PtcLayerDev L, const bf16 *in,
-                                                                      const float *delta, float *partial, int par,
-                                                                      int groups) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int KROW = 2 * 48 + kLdsPad;  // k = 2*n + r', n = colour*16 + site
-  __bf16 *At = reinterpret_cast<__bf16 *>(smem);             // [Mpad][KROW]  (delta embedding)
-  const int mrows = L.mw_tiles * 16;
-  __bf16 *Bt = At + mrows * KROW;                             // [chunk_ch*36][KROW]  (Y' transposed)
-  const int ck = blockIdx.y;
-  const int grp = blockIdx.x;
+template <int RC, bool PATH, int JW>
+__global__ void __launch_bounds__(kWgThreads)
+ptc_bwd_weight_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, const bf16 *__restrict__ in,
+                      const bf16 *__restrict__ delta, float *__restrict__ partial, int groups, int zero_par) {
+  __shared__ __align__(16) __bf16 At[2][64 * kWgRow];
+  __shared__ __align__(16) __bf16 Bt[2][64 * kWgRow];
+  // the chunks of one group of tiles run side by side on one XCD (the
+  // dispatcher deals workgroups round-robin over 8), so that they share its L2
+  const int nck = gridDim.y, b8 = blockIdx.x + gridDim.x * blockIdx.y, loc = b8 / 8;
+  const int grp = (b8 % 8) * (groups / 8) + loc / nck, ck = loc % nck;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ncol = L.chunk_ch * 36;        // k' in this chunk
-  const int ntiles_n = (ncol + 15) / 16;
-  const int ntile_total = L.mw_tiles * ntiles_n;
-  f32x4_t acc[24];
+  const int sl = threadIdx.x & 15, it = threadIdx.x >> 4;
+  const int64_t vh = q.g.Vh, vs = vh * L.cin;
+  // items beyond the last and channels beyond Cout (rows and columns of the
+  // result that are not used) repeat the first
+  const int qi = 16 * ck + it < L.fw_items ? 16 * ck + it : 0;
+  const int p = PATH ? ck : qi / L.cin, i = PATH ? it : qi - p * L.cin, o = it < L.cout ? it : 0;
+  const int ph_ = p == 0 ? 1 : p, mu = (ph_ - 1) >> 1;
+  const bool fwd = ((ph_ - 1) & 1) == 0;
+  const int ntile = (int)((vh + kTile - 1) / kTile);
+  // tiles of both parities in turn, or those of the parity where delta lives
+  const int npar = zero_par < 0 ? 2 : 1, total = npar * ntile;
+  const int first = (int)((int64_t)grp * total / groups), last = (int)((int64_t)(grp + 1) * total / groups) - 1;
+  const int nmt = L.mw_tiles, wm = wave & 1, wn = wave >> 1;
+
+  f32x4_t acc[JW][2];
 #pragma unroll
-  for (int t = 0; t < 24; ++t) acc[t] = f32x4_t{0, 0, 0, 0};
-  const int ntile_sites = (q.g.Vh + kTile - 1) / kTile;
-  const int64_t vsd = (int64_t)q.g.Vh * L.cout;
-  const float *dblk = delta + (int64_t)par * vsd * 24;
-  for (int tile = grp; tile < ntile_sites; tile += groups) {
-    const int s0 = tile * kTile;
-    __syncthreads();
-    for (int e = threadIdx.x; e < (mrows + ntiles_n * 16) * KROW; e += kPtcThreads) At[e] = (__bf16)0.f;
-    __syncthreads();
-    // delta -> A: row 2*(o*4+s)+r, col 2*(c*16+sl)+r'
-    for (int it = threadIdx.x; it < kTile * L.cout; it += kPtcThreads) {
-      const int sl = it / L.cout, o = it % L.cout;
-      const int s = s0 + sl;
-      if (s >= q.g.Vh) continue;
-      float r[24];
-      load_spinor_reals<float, 24, float>(dblk, vsd, (int64_t)s * L.cout + o, r);
+  for (int j = 0; j < JW; ++j)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[j][t] = f32x4_t{0, 0, 0, 0};
+
+  auto run = [&](auto ident) __attribute__((always_inline)) {
+    constexpr bool IDENT = decltype(ident)::value;  // every item of the chunk is on the identity path
+    uint4 dr[3], yr[3];
+    float lv[RC];
+    float ph = 1.f;
+    // (tiles and sites beyond the last are clamped; such sites' delta is zeroed)
+    auto site_of = [&](int tile) { return (npar == 2 ? tile >> 1 : tile) * kTile + sl; };
+    auto clamped = [&](int tile) { return min(site_of(tile), (int)vh - 1); };
+    auto par_of = [&](int tile) { return npar == 2 ? (tile & 1) : 1 - zero_par; };
+    // the site that path p reaches (loaded a tile ahead of the operands)
+    auto entry = [&](int tile) {
+      const int s = clamped(tile);
+      if constexpr (IDENT) return s;
+      const int e = nbr[((int64_t)par_of(tile) * 8 + ph_ - 1) * vh + s];
+      return PATH || p != 0 ? e : s;
+    };
+    auto fetch = [&](int tile, int e) __attribute__((always_inline)) {
+      const int par = par_of(tile), s = clamped(tile), n = e & 0x7fffffff;
+      const uint4 *d = delta_at(delta, vh, L.cout, par, s, o);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) dr[c] = d[c * L.cout];
+      if constexpr (!IDENT) {
+        ph = e < 0 ? -1.f : 1.f;
+        load_site<float, RC, float>(q.gauge + (int64_t)(2 * mu + (fwd ? par : 1 - par)) * vh * RC, vh, fwd ? s : n,
+                                    lv);
+      }
+      const bf16 *blk = in + (int64_t)(p == 0 ? par : 1 - par) * vs * 24;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        yr[c] = *reinterpret_cast<const uint4 *>(blk + ((int64_t)c * vs + (int64_t)n * L.cin + i) * 8);
+    };
+    if (last < first) return;
+    int buf = 0, e1 = entry(first);
+    fetch(first, e1);
+    e1 = entry(min(first + 1, last));
+#pragma unroll 1
+    for (int tile = first; tile <= last; ++tile, buf ^= 1) {
+      // words: delta [colour][spin], Y [spin][colour]
+      uint32_t dw[12], yw[12];
+      const bool valid = site_of(tile) < vh;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        dw[4 * c] = dr[c].x, dw[4 * c + 1] = dr[c].y, dw[4 * c + 2] = dr[c].z, dw[4 * c + 3] = dr[c].w;
+        yw[4 * c] = yr[c].x, yw[4 * c + 1] = yr[c].y, yw[4 * c + 2] = yr[c].z, yw[4 * c + 3] = yr[c].w;
+      }
+      __bf16 *Ab = At[buf] + 4 * it * kWgRow + 2 * sl, *Bb = Bt[buf] + 4 * it * kWgRow + 2 * sl;
+#pragma unroll
       for (int sp = 0; sp < 4; ++sp)
-        for (int c = 0; c < 3; ++c) {
-          const float dr = r[6 * sp + 2 * c], di = r[6 * sp + 2 * c + 1];
-          const int row = 2 * (o * 4 + sp), col = 2 * (c * kTile + sl);
-          At[row * KROW + col] = (__bf16)dr;
-          At[row * KROW + col + 1] = (__bf16)di;
-          At[(row + 1) * KROW + col] = (__bf16)di;
-          At[(row + 1) * KROW + col + 1] = (__bf16)(-dr);
-        }
-    }
-    // Y' -> B (stored [k'][k]): transported inputs of this channel chunk
-    const int nitem = kTile * L.chunk_ch * 9;
-    for (int it = threadIdx.x; it < nitem; it += kPtcThreads) {
-      const int sl = it % kTile, rem = it / kTile, p = rem % 9, il = rem / 9;
-      const int i = ck * L.chunk_ch + il;
-      const int s = s0 + sl;
-      if (s >= q.g.Vh || i >= L.cin) continue;
-      const Site x = decode_site(q.g, s, par);
-      cpx<float> y[4][3];
-      transport_any(q, in, L.cin, i, p, x, s, y);
-      for (int sp = 0; sp < 4; ++sp) {
-        const int kp = (il * 9 + p) * 4 + sp;
-        for (int c = 0; c < 3; ++c) {
-          const int col = 2 * (c * kTile + sl);
-          Bt[kp * KROW + col] = (__bf16)y[sp][c].re;
-          Bt[kp * KROW + col + 1] = (__bf16)y[sp][c].im;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          *reinterpret_cast<uint32_t *>(Ab + sp * kWgRow + 2 * c * kTile) = valid ? dw[4 * c + sp] : 0u;
+      if constexpr (IDENT) {
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) *reinterpret_cast<uint32_t *>(Bb + sp * kWgRow + 2 * c * kTile) = yw[3 * sp + c];
+      } else {
+        const Link<float> U0 = unpack_link<RC, float>(lv);
+        // U, or U^+ for a backward hop, times the boundary sign, on one spin at a time
+        auto apply = [&](auto adj) __attribute__((always_inline)) {
+#pragma unroll
+          for (int sp = 0; sp < 4; ++sp) {
+            cpx<float> v[3], u[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const uint32_t w = yw[3 * sp + c];
+              v[c] = mk<float>(__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u));
+            }
+            if constexpr (decltype(adj)::value)
+              su3_adj_mv(U0, v, u);
+            else
+              su3_mv(U0, v, u);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const uint32_t w = __builtin_bit_cast(uint32_t, pack_bf16x2(ph * u[c].re, ph * u[c].im));
+              *reinterpret_cast<uint32_t *>(Bb + sp * kWgRow + 2 * c * kTile) = PATH || p != 0 ? w : yw[3 * sp + c];
+            }
+          }
+        };
+        if (fwd)
+          apply(std::false_type());
+        else
+          apply(std::true_type());
+      }
+      fetch(min(tile + 1, last), e1);
+      e1 = entry(min(tile + 2, last));
+      __syncthreads();  // this tile is in LDS (and the last but one has been multiplied)
+#pragma unroll
+      for (int ks = 0; ks < 3; ++ks) {
+        bf16x8_t b[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          b[t] = lds_frag(Bt[buf] + ((2 * wn + t) * 16 + (lane & 15)) * kWgRow + ks * 32 + 8 * (lane >> 4));
+#pragma unroll
+        for (int j = 0; j < JW; ++j) {
+          const int mt = wm + 2 * j;
+          // row 16 mt + lane % 16 = 2 (channel, spin) + r
+          uint4 w = *reinterpret_cast<const uint4 *>(At[buf] + (8 * mt + ((lane & 15) >> 1)) * kWgRow + ks * 32 +
+                                                     8 * (lane >> 4));
+          if (lane & 1) {  // (dr, di) -> (di, -dr)
+            w.x = ((w.x >> 16) | (w.x << 16)) ^ 0x80000000u;
+            w.y = ((w.y >> 16) | (w.y << 16)) ^ 0x80000000u;
+            w.z = ((w.z >> 16) | (w.z << 16)) ^ 0x80000000u;
+            w.w = ((w.w >> 16) | (w.w << 16)) ^ 0x80000000u;
+          }
+          const bf16x8_t a = __builtin_bit_cast(bf16x8_t, w);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) acc[j][t] = mfma_bf16(a, b[t], acc[j][t]);
         }
       }
     }
-    __syncthreads();
-    for (int ks = 0; ks < 3; ++ks) {
+  };
+  if (PATH && ck == 0)
+    run(std::true_type());
+  else
+    run(std::false_type());
+  // partial[ck][grp][16 mw_tiles rows][64 columns (item, spin)]
+  float *dst = partial + ((size_t)ck * groups + grp) * (size_t)nmt * 16 * 64;
 #pragma unroll
-      for (int t = 0; t < 24; ++t) {
-        const int tid = wave + 4 * t;
-        if (tid < ntile_total) {
-          const int mt = tid / ntiles_n, nt = tid % ntiles_n;
-          const bf16x8_t a = lds_frag(At + (mt * 16 + (lane & 15)) * KROW + ks * 32 + 8 * (lane >> 4));
-          const bf16x8_t b = lds_frag(Bt + (nt * 16 + (lane & 15)) * KROW + ks * 32 + 8 * (lane >> 4));
-          acc[t] = mfma_bf16(a, b, acc[t]);
-        }
-      }
-    }
-  }
-  // partial[ck][grp][row][col]
-  float *dst = partial + ((size_t)ck * groups + grp) * (size_t)mrows * (ntiles_n * 16);
+  for (int j = 0; j < JW; ++j) {
+    const int mt = wm + 2 * j;
+    if (mt >= nmt) continue;
 #pragma unroll
-  for (int t = 0; t < 24; ++t) {
-    const int tid = wave + 4 * t;
-    if (tid < ntile_total) {
-      const int mt = tid / ntiles_n, nt = tid % ntiles_n;
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = mt * 16 + 4 * (lane >> 4) + j, col = nt * 16 + (lane & 15);
-        dst[(size_t)row * (ntiles_n * 16) + col] = acc[t][j];
-      }
-    }
+      for (int jj = 0; jj < 4; ++jj)
+        dst[(16 * mt + 4 * (lane >> 4) + jj) * 64 + (2 * wn + t) * 16 + (lane & 15)] = acc[j][t][jj];
   }
 }
 
-// gW[o][i][p][s][s'] (complex, FP32) += sum over groups of the partials, in a
-// fixed order (deterministic).
-__global__ void ptc_weight_reduce_kernel(PtcLayerDev L, const float *partial, int groups, float *gw, int accumulate) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;  // complex entry index
-  const int total = L.cout * L.cin * 9 * 16;
-  if (idx >= total) return;
-  const int sp2 = idx % 4, sp = (idx / 4) % 4, p = (idx / 16) % 9, i = (idx / 144) % L.cin, o = idx / (144 * L.cin);
-  const int ck = i / L.chunk_ch, il = i - ck * L.chunk_ch;
-  const int ncol = L.chunk_ch * 36, ldc = ((ncol + 15) / 16) * 16;
-  const int mrows = L.mw_tiles * 16;
-  const int col = (il * 9 + p) * 4 + sp2;
-  const int row = 2 * (o * 4 + sp);
+// gW[o][i][p][s][s'] (complex, FP32) = sum over groups of the partials, in a
+// fixed order: a quarter of the groups per thread, then the four sums. 64
+// threads run along a row of the partials (one chunk's columns).
+__global__ void __launch_bounds__(256) ptc_weight_reduce_kernel(PtcLayerDev L, const float *partial, int groups,
+                                                                float *gw) {
+  __shared__ double sum[4][64][2];
+  const int col = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int m = blockIdx.x, ck = blockIdx.y;  // m = 4 o + s
+  const size_t ld = (size_t)L.mw_tiles * 16 * 64;
+  const float *base = partial + (size_t)ck * groups * ld + (size_t)2 * m * 64 + col;
+  const int g0 = part * groups / 4, g1 = (part + 1) * groups / 4;
   double re = 0, im = 0;
-  for (int g = 0; g < groups; ++g) {
-    const float *base = partial + ((size_t)ck * groups + g) * (size_t)mrows * ldc;
-    re += base[(size_t)row * ldc + col];
-    im += base[(size_t)(row + 1) * ldc + col];
+#pragma unroll 4
+  for (int g = g0; g < g1; ++g) {
+    re += base[g * ld];
+    im += base[g * ld + 64];
   }
-  if (accumulate) {
-    gw[2 * idx] += (float)re;
-    gw[2 * idx + 1] += (float)im;
-  } else {
-    gw[2 * idx] = (float)re;
-    gw[2 * idx + 1] = (float)im;
-  }
+  sum[part][col][0] = re;
+  sum[part][col][1] = im;
+  __syncthreads();
+  const int qi = 16 * ck + (col >> 2);
+  if (part != 0 || qi >= L.fw_items) return;
+  const int p = qi / L.cin, i = qi - p * L.cin, o = m >> 2, s = m & 3;
+  const size_t idx = ((((size_t)o * L.cin + i) * 9 + p) * 4 + s) * 4 + (col & 3);
+  gw[2 * idx] = (float)(((sum[0][col][0] + sum[1][col][0]) + sum[2][col][0]) + sum[3][col][0]);
+  gw[2 * idx + 1] = (float)(((sum[0][col][1] + sum[1][col][1]) + sum[2][col][1]) + sum[3][col][1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -910,7 +1021,7 @@ __global__ void ptc_pack_forward_kernel(PtcLayerDev L, const float *W, bf16x8_t 
   A[idx] = v;
 }
 
-// adjoint A: row m = 2*((i*9+p)*4+s') + r, col k = 2*(o*4+s) + r'; conj(W)^T embedded.
+// adjoint A: row m = 2*((p*Cin+i)*4+s') + r, col k = 2*(o*4+s) + r'; conj(W)^T embedded.
 __global__ void ptc_pack_adjoint_kernel(PtcLayerDev L, const float *W, bf16x8_t *A) {
   const int ks_n = L.kadj / 32;
   const int total = L.madj_tiles * ks_n * 64;
@@ -919,13 +1030,13 @@ __global__ void ptc_pack_adjoint_kernel(PtcLayerDev L, const float *W, bf16x8_t 
   const int lane = idx % 64, ks = (idx / 64) % ks_n, mt = idx / (64 * ks_n);
   const int m = mt * 16 + (lane & 15);
   const int kp = m >> 1, r = m & 1;
-  const int i = kp / 36, p = (kp / 4) % 9, s2 = kp & 3;
+  const int qi = kp >> 2, p = qi / L.cin, i = qi - p * L.cin, s2 = kp & 3;
   bf16x8_t v;
   for (int j = 0; j < 8; ++j) {
     const int k = ks * 32 + 8 * (lane >> 4) + j;
     const int mp = k >> 1, r2 = k & 1, o = mp >> 2, s = mp & 3;
     float val = 0.f;
-    if (i < L.cin && o < L.cout) {
+    if (p < 9 && o < L.cout) {
       const float wr = wval(W, L.cin, o, i, p, s, s2, 0), wi = wval(W, L.cin, o, i, p, s, s2, 1);
       // conj(W)^T: [[Wr, Wi], [-Wi, Wr]]
       val = (r == 0) ? (r2 == 0 ? wr : wi) : (r2 == 0 ? -wi : wr);
@@ -937,12 +1048,6 @@ __global__ void ptc_pack_adjoint_kernel(PtcLayerDev L, const float *W, bf16x8_t 
 
 // ---------------------------------------------------------------------------
 // host launchers
-
-size_t ptc_bwd_data_lds(const PtcLayerDev &L) { return 48 * (L.kadj + kLdsPad) * 2; }
-size_t ptc_bwd_weight_lds(const PtcLayerDev &L) {
-  const int ncol = L.chunk_ch * 36, ntn = (ncol + 15) / 16;
-  return (size_t)(L.mw_tiles * 16 + ntn * 16) * (2 * 48 + kLdsPad) * 2;
-}
 
 hipError_t launch_ptc_nbr(const Geom &g, int *tab, hipStream_t st) {
   if (g.Vh == 0) return hipSuccess;
@@ -1014,32 +1119,89 @@ hipError_t launch_ptc_input(int64_t vh, const void *in_even, void *act, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_ptc_bwd_data(const PtcGeo &q, const PtcLayerDev &L, const float *delta, float *gy, int par,
-                               hipStream_t st) {
-  const int nt = (q.g.Vh + kTile - 1) / kTile;
-  hipLaunchKernelGGL(ptc_bwd_data_kernel, dim3(nt), dim3(kPtcThreads), ptc_bwd_data_lds(L), st, q, L, delta, gy, par);
+hipError_t launch_ptc_delta(int64_t vh, const float *in_even, void *delta, hipStream_t st) {
+  hipLaunchKernelGGL(ptc_delta_kernel, dim3((unsigned)((vh + 255) / 256)), dim3(256), 0, st, vh, in_even, (bf16 *)delta);
   return hipGetLastError();
 }
 
-hipError_t launch_ptc_adjoint_gather(const PtcGeo &q, int cin, const float *gy, float *gpsi, int par,
-                                     hipStream_t st) {
-  const int n = q.g.Vh * cin, bt = 256;
-  hipLaunchKernelGGL(ptc_adjoint_gather_kernel, dim3((n + bt - 1) / bt), dim3(bt), 0, st, q, cin, gy, gpsi, par);
+hipError_t launch_ptc_bwd_data(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *delta, void *gpsi,
+                               int zero_par, hipStream_t st) {
+  const dim3 grid(2 * ((q.g.Vh + kBwSites - 1) / kBwSites));
+  const int nmt = (8 * L.cin + 15) / 16, nks = L.kadj / 32;
+#define PTC_DY(RC, MT, KS)                                                                                \
+  hipLaunchKernelGGL((ptc_bwd_data_kernel<RC, MT, KS>), grid, dim3(kBwThreads), 0, st, q, L, nbr,          \
+                     (const bf16 *)delta, (bf16 *)gpsi, zero_par)
+#define PTC_DY_KS(RC, MT)   \
+  if (nks == 1)             \
+    PTC_DY(RC, MT, 1);      \
+  else if (nks == 2)        \
+    PTC_DY(RC, MT, 2);      \
+  else                      \
+    PTC_DY(RC, MT, 4)
+#define PTC_DY_MT(RC)       \
+  if (nmt <= 2) {           \
+    PTC_DY_KS(RC, 2);       \
+  } else if (nmt <= 4) {    \
+    PTC_DY_KS(RC, 4);       \
+  } else {                  \
+    PTC_DY_KS(RC, 8);       \
+  }
+  if (q.recon == 12) {
+    PTC_DY_MT(12)
+  } else {
+    PTC_DY_MT(18)
+  }
+#undef PTC_DY_MT
+#undef PTC_DY_KS
+#undef PTC_DY
   return hipGetLastError();
 }
 
-hipError_t launch_ptc_bwd_weight(const PtcGeo &q, const PtcLayerDev &L, const void *in, const float *delta,
-                                 float *partial, int par, int groups, hipStream_t st) {
-  hipLaunchKernelGGL(ptc_bwd_weight_kernel, dim3(groups, L.nchunk), dim3(kPtcThreads), ptc_bwd_weight_lds(L), st, q,
-                     L, (const bf16 *)in, delta, partial, par, groups);
-  return hipGetLastError();
+int ptc_weight_chunks(const PtcLayerDev &L) { return (L.fw_items + 15) / 16; }
+
+// Three workgroups per CU fit (LDS, registers): their number over all chunks
+// stays at or below 768, so that no second wave of a few workgroups follows
+// (792 took twice the time of 720). A multiple of 8, one share per XCD, and no
+// more than there are tiles (rounded up: a group may be empty).
+int ptc_weight_groups(const PtcLayerDev &L, size_t vh, int zero_par) {
+  const size_t tiles = (zero_par < 0 ? 2 : 1) * ((vh + kTile - 1) / kTile);
+  const size_t most = 768 / ptc_weight_chunks(L) / 8 * 8;
+  return (int)std::min(most, (tiles + 7) / 8 * 8);
+}
+size_t ptc_weight_partial_bytes(const PtcLayerDev &L, size_t vh, int zero_par) {
+  return (size_t)ptc_weight_chunks(L) * ptc_weight_groups(L, vh, zero_par) * L.mw_tiles * 16 * 64 * sizeof(float);
 }
 
-hipError_t launch_ptc_weight_reduce(const PtcLayerDev &L, const float *partial, int groups, float *gw, int accumulate,
-                                    hipStream_t st) {
-  const int total = L.cout * L.cin * 9 * 16, bt = 256;
-  hipLaunchKernelGGL(ptc_weight_reduce_kernel, dim3((total + bt - 1) / bt), dim3(bt), 0, st, L, partial, groups, gw,
-                     accumulate);
+hipError_t launch_ptc_bwd_weight(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *in,
+                                 const void *delta, float *partial, float *gw, int zero_par, hipStream_t st) {
+  const int groups = ptc_weight_groups(L, q.g.Vh, zero_par), nck = ptc_weight_chunks(L);
+#define PTC_DW(RC, PATH, JW)                                                                                      \
+  hipLaunchKernelGGL((ptc_bwd_weight_kernel<RC, PATH, JW>), dim3(groups, nck), dim3(kWgThreads), 0, st, q, L, nbr, \
+                     (const bf16 *)in, (const bf16 *)delta, partial, groups, zero_par)
+#define PTC_DW_JW(RC, PATH) \
+  if (L.mw_tiles <= 2)      \
+    PTC_DW(RC, PATH, 1);    \
+  else if (L.mw_tiles <= 4) \
+    PTC_DW(RC, PATH, 2);    \
+  else                      \
+    PTC_DW(RC, PATH, 4)
+  if (q.recon == 12) {
+    if (L.cin == 16) {
+      PTC_DW_JW(12, true);
+    } else {
+      PTC_DW_JW(12, false);
+    }
+  } else {
+    if (L.cin == 16) {
+      PTC_DW_JW(18, true);
+    } else {
+      PTC_DW_JW(18, false);
+    }
+  }
+#undef PTC_DW_JW
+#undef PTC_DW
+  hipLaunchKernelGGL(ptc_weight_reduce_kernel, dim3(4 * L.cout, nck), dim3(256), 0, st, L, (const float *)partial,
+                     groups, gw);
   return hipGetLastError();
 }
 

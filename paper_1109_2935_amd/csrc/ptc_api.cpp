@@ -175,26 +175,22 @@ static lqcd_status ptc_backprop(lqcd_context *ctx, const lqcd_operator *op, cons
   std::vector<void *> acts;
   TRY(ptc_buffers(ctx, plan, info, kSlotPtc, acts));
   TRY(ptc_forward_all(ctx, plan, q, info, r_even, acts, acts[plan.nl], st));
-  int maxc = 1, maxc9 = 9;
-  for (auto &L : plan.layers) {
-    maxc = std::max(maxc, std::max(L.cin, L.cout));
-    maxc9 = std::max(maxc9, 9 * L.cin);
-  }
-  void *d0, *d1, *gy, *part;
-  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 1, 2 * vh * 24 * maxc * sizeof(float), &d0));
-  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 2, 2 * vh * 24 * maxc * sizeof(float), &d1));
-  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 3, 2 * vh * 24 * (size_t)maxc9 * sizeof(float), &gy));
-  const int groups = 128;
+  int maxc = 1;
   size_t pbytes = 0;
-  for (auto &L : plan.layers) {
-    const size_t ldc = (size_t)((L.chunk_ch * 36 + 15) / 16) * 16;
-    pbytes = std::max(pbytes, (size_t)L.nchunk * groups * L.mw_tiles * 16 * ldc * sizeof(float));
+  for (int l = 0; l < plan.nl; ++l) {
+    const PtcLayerDev &L = plan.layers[l];
+    maxc = std::max(maxc, L.cin);
+    pbytes = std::max(pbytes, ptc_weight_partial_bytes(L, vh, l == plan.nl - 1 ? 1 : -1));
   }
+  void *dy, *d0, *d1, *part, *nbr;
+  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 3, vh * 24 * sizeof(float), &dy));
+  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 1, 2 * vh * 24 * maxc * sizeof(uint16_t), &d0));
+  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 2, 2 * vh * 24 * maxc * sizeof(uint16_t), &d1));
   TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 4, pbytes, &part));
+  TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 5, 2 * 8 * vh * sizeof(int), &nbr));  // filled by the forward pass
   RedScratch red = red_scratch(ctx);
   const size_t n = vh * 12;  // complex entries of one even field
-  float *delta = (float *)d0;
-  TRY(hip_check(ctx, hipMemsetAsync(delta, 0, 2 * vh * 24 * sizeof(float), st), "memset"));
+  float *delta = (float *)dy;  // dL/d conj(y) on even sites
   if (kind == kLossError) {
     // loss = |y - e|^2 / |e|^2 on even sites; delta = dL/d conj(y) = (y - e) / |e|^2
     const void *e_even = aux;
@@ -227,22 +223,17 @@ static lqcd_status ptc_backprop(lqcd_context *ctx, const lqcd_operator *op, cons
     // the caller's cotangent dL/d conj(y) on even sites
     TRY(hip_check(ctx, hipMemcpyAsync(delta, aux, vh * 24 * sizeof(float), hipMemcpyDeviceToDevice, st), "copy"));
   }
-  // backward through the layers
-  float *dcur = (float *)d0, *dnext = (float *)d1;
+  // backward through the layers; the last layer's cotangent lives on even sites
+  void *dcur = d0, *dnext = d1;
+  TRY(hip_check(ctx, launch_ptc_delta((int64_t)vh, delta, dcur, st), "ptc delta"));
   for (int l = plan.nl - 1; l >= 0; --l) {
     const PtcLayerDev &L = plan.layers[l];
-    const bool last = l == plan.nl - 1;
+    const int zero_par = l == plan.nl - 1 ? 1 : -1;
     float *gw = (float *)grad + 2 * plan.woff[l];
-    for (int par = 0; par < (last ? 1 : 2); ++par) {
-      TRY(hip_check(ctx, launch_ptc_bwd_weight(q, L, acts[l], dcur, (float *)part, par, groups, st), "ptc dW"));
-      TRY(hip_check(ctx, launch_ptc_weight_reduce(L, (const float *)part, groups, gw, par, st), "ptc dW reduce"));
-    }
+    TRY(hip_check(ctx, launch_ptc_bwd_weight(q, L, (const int *)nbr, acts[l], dcur, (float *)part, gw, zero_par, st),
+                  "ptc dW"));
     if (l == 0) break;
-    TRY(hip_check(ctx, hipMemsetAsync(gy, 0, 2 * vh * 24 * (size_t)(9 * L.cin) * sizeof(float), st), "memset"));
-    for (int par = 0; par < (last ? 1 : 2); ++par)
-      TRY(hip_check(ctx, launch_ptc_bwd_data(q, L, dcur, (float *)gy, par, st), "ptc dY"));
-    for (int par = 0; par < 2; ++par)
-      TRY(hip_check(ctx, launch_ptc_adjoint_gather(q, L.cin, (const float *)gy, dnext, par, st), "ptc adjoint"));
+    TRY(hip_check(ctx, launch_ptc_bwd_data(q, L, (const int *)nbr, dcur, dnext, zero_par, st), "ptc dY"));
     std::swap(dcur, dnext);
   }
   return LQCD_OK;

@@ -241,3 +241,25 @@ def test_learned_fgcr_falls_back_to_schwarz(ctx, bad, cycles):
     with pytest.raises(L.LqcdError) as ei:
         L.lqcd_gcr_solve(ctx, o[0].op, o[1].op, o[1].op, prm0, x0, bp)
     assert ei.value.status == L.LQCD_ERR_BREAKDOWN
+
+
+# the backward kernels' tile counts (m-tiles of 2 input channels, K steps of 4
+# output channels, chunks of 16 items that are a path or not) at channel counts
+# on both sides of each, both link formats, on lattices that leave part of a
+# 16-site tile, of a 64-site workgroup or neither empty
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 2, 4), (4, 4, 4, 4)])
+@pytest.mark.parametrize("channels", [(1, 3, 1), (1, 2, 4, 1), (1, 8, 12, 1), (1, 12, 16, 1), (1, 16, 8, 1), (1, 16, 2, 1)])
+def test_ptc_gradient_every_tiling(ctx, channels, dims, recon):
+    U = synth.gauge_field(dims, 0.25, 141)
+    op32 = ops.wilson_clover(ctx, U, dims, 0.124, 1.0, 1, recon)
+    even = oracle.parity_mask(dims, 0)
+    net = ptc.Network(ctx, channels)
+    Ws = weights_c64(optc.init_weights(142, channels=channels))
+    net.set_weights(Ws)
+    r = on_parity(synth.gaussian_spinor(dims, 143), even)
+    dy = on_parity(synth.gaussian_spinor(dims, 144), even)
+    net.vjp(op32, op32.import_spinor(r, 0), op32.import_spinor(dy, 0))
+    gref = optc.vjp(dims, U, r, dy, Ws, even)
+    for k, (g, G) in enumerate(zip(_flat_grads(net, gref), gref)):
+        check_entries(g, G, GRAD_TOL, "layer %d" % k)
