@@ -371,3 +371,30 @@ def test_invalid_arguments_write_nothing(ctx):
     assert ei.value.status == L.LQCD_ERR_INVALID_ARG
     torch.cuda.synchronize()
     assert bool((out == 7).all())
+
+
+# the clover build takes 64 sites per workgroup, in columns along t of the
+# largest even extents up to 8 that divide Ly and Lz: lattices that end inside a
+# workgroup, columns of 2, 6 and 8, extents of 2 (both neighbours are one site)
+@pytest.mark.parametrize("dims,tile", [((2, 2, 2, 2), None), ((6, 2, 10, 2), (2, 2, 10, 2)), ((2, 14, 6, 4), None),
+                                       ((4, 8, 16, 2), (4, 4, 8, 2))])
+@pytest.mark.parametrize("prec,recon", [(0, 18), (2, 12), (3, 18)])
+def test_clover_build_edges(ctx, dims, tile, prec, recon):
+    U, psi, _ = Fields.get(dims)
+    o = make_op(ctx, dims, prec, recon, tile)
+    A = oracle.clover_build(dims, U, 0.124, 1.0)
+    for inverse, M in ((0, A), (1, oracle.clover_invert(dims, A))):
+        for p in (0, 1):
+            src = on_parity(psi, oracle.parity_mask(dims, p))
+            out = o.spinor()
+            L.lqcd_clover_apply(ctx, o.op, out, o.import_spinor(src, p), p, inverse)
+            check(np_of(o.export_spinor(out, p)), oracle.clover_apply(dims, M, src, parity=p), TOL[prec])
+
+
+def test_clover_build_refuses_indefinite_blocks(ctx):
+    """A clover term with an eigenvalue below zero has no inverse here."""
+    dims = (4, 4, 2, 2)
+    U = synth.gauge_field(dims, 1.0, 17)
+    with pytest.raises(L.LqcdError) as ei:
+        ops.wilson_clover(ctx, U, dims, 0.5, 8.0, 0, 18)
+    assert ei.value.status == L.LQCD_ERR_BREAKDOWN
