@@ -194,6 +194,7 @@ lqcd_status wilson_hop(lqcd_context *ctx, const OpInfo &info, const Geom &g, int
   w.nrhs = nrhs;
   w.mfma = use_mfma(info.prec, nrhs, partials) ? 1 : 0;
   w.block_threads = 256;
+  if (wilson_split_fits(w)) return hip_check(ctx, launch_wilson_split(w, st), "wilson dslash launch");
   // Workgroup size picked by the autotuner per (kernel, precision, links,
   // geometry, rhs). Calls that overwrite one of their inputs are not re-run
   // for timing; they use the tuned value if there is one, else 128.

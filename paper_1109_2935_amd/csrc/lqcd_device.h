@@ -254,14 +254,21 @@ template <typename R> struct cpx {
 template <typename R> __device__ __forceinline__ cpx<R> mk(R a, R b) { return cpx<R>{a, b}; }
 template <typename R> __device__ __forceinline__ cpx<R> operator+(cpx<R> a, cpx<R> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename R> __device__ __forceinline__ cpx<R> operator-(cpx<R> a, cpx<R> b) { return {a.re - b.re, a.im - b.im}; }
+// Products with the fused operation written out, here and below: which of the
+// two products the compiler would fuse depends on the code around it, and the
+// kernels that share this code give the same result bit for bit.
 template <typename R> __device__ __forceinline__ cpx<R> operator*(cpx<R> a, cpx<R> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
 }
 template <typename R> __device__ __forceinline__ cpx<R> operator*(R s, cpx<R> a) { return {s * a.re, s * a.im}; }
 template <typename R> __device__ __forceinline__ cpx<R> conj(cpx<R> a) { return {a.re, -a.im}; }
 // conj(a) * b
 template <typename R> __device__ __forceinline__ cpx<R> cmul_conj(cpx<R> a, cpx<R> b) {
-  return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
+}
+// s * a + b
+template <typename R> __device__ __forceinline__ cpx<R> scale_add(R s, cpx<R> a, cpx<R> b) {
+  return {fma(s, a.re, b.re), fma(s, a.im, b.im)};
 }
 // i * a
 template <typename R> __device__ __forceinline__ cpx<R> times_i(cpx<R> a) { return {-a.im, a.re}; }

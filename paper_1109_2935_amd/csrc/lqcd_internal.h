@@ -92,6 +92,10 @@ struct WilsonLaunch {
   int mfma;          // link products on the matrix cores (16-bit, nrhs % 4 == 0, no partials)
 };
 hipError_t launch_wilson(const WilsonLaunch &w, hipStream_t st);
+// The form for launches with few points (wilson_split.hip), the same result bit
+// for bit; block_threads is not used.
+bool wilson_split_fits(const WilsonLaunch &w);
+hipError_t launch_wilson_split(const WilsonLaunch &w, hipStream_t st);
 
 // Persistent multi-operator hopping term (mode W_HOP, coef 1).
 struct BatchJob {

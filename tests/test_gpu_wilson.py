@@ -398,3 +398,31 @@ def test_clover_build_refuses_indefinite_blocks(ctx):
     with pytest.raises(L.LqcdError) as ei:
         ops.wilson_clover(ctx, U, dims, 0.5, 8.0, 0, 18)
     assert ei.value.status == L.LQCD_ERR_BREAKDOWN
+
+
+# launches of at most 16384 points (site, source) run a site's hops in eight
+# waves, larger ones one site per thread: 6 sources of 2560 sites are the first,
+# 8 the second, and both equal the single-source launches bit for bit
+@pytest.mark.parametrize("prec,recon", [(0, 18), (0, 12), (0, 8), (1, 18), (1, 12), (1, 8)])
+@pytest.mark.parametrize("block", [None, (4, 4, 4, 10)])
+@pytest.mark.parametrize("dagger", [0, 1])
+def test_split_launch_equals_plain(ctx, prec, recon, block, dagger):
+    dims = (8, 8, 8, 10)
+    o = make_op(ctx, dims, prec, recon, (4, 4, 2, 10))
+    fields = np.stack([synth.gaussian_spinor(dims, 400 + j) for j in range(8)])
+    for n in (6, 8):
+        for p in (0, 1):
+            src = np.stack([on_parity(f, oracle.parity_mask(dims, p)) for f in fields[:n]])
+            inp, hop, schur = o.import_spinor(src, p, nrhs=n), o.spinor(nrhs=n), o.spinor(nrhs=n)
+            L.lqcd_dslash(ctx, o.op, hop, inp, 1 - p, dagger, block=block, nrhs=n)
+            got = [np_of(o.export_spinor(hop, 1 - p, nrhs=n))]
+            if p == 0:
+                L.lqcd_schur_apply(ctx, o.op, schur, inp, dagger, block=block, nrhs=n)
+                got.append(np_of(o.export_spinor(schur, 0, nrhs=n)))
+            for j in range(n):
+                one, out = o.import_spinor(src[j], p), o.spinor()
+                L.lqcd_dslash(ctx, o.op, out, one, 1 - p, dagger, block=block)
+                assert np.array_equal(got[0][j], np_of(o.export_spinor(out, 1 - p)))
+                if p == 0:
+                    L.lqcd_schur_apply(ctx, o.op, out, one, dagger, block=block)
+                    assert np.array_equal(got[1][j], np_of(o.export_spinor(out, 0)))
