@@ -438,8 +438,8 @@ lqcd_status lqcd_context_create(lqcd_context **out) {
   noalloc_init_device(ctx->device);
   lqcd_status s = LQCD_OK;
   if (hipMalloc(&ctx->red_partials, 1024 * kMaxRed * sizeof(double)) != hipSuccess ||
-      hipHostMalloc(&ctx->red_host, kMaxRed * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
-          hipSuccess)
+      hipHostMalloc(&ctx->red_host, kMaxRed * sizeof(double) + kCgRing * sizeof(CgRing),
+                    hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     s = LQCD_ERR_OUT_OF_MEMORY;
   if (!s && hipHostGetDevicePointer((void **)&ctx->red_host_dev, ctx->red_host, 0) != hipSuccess)
     s = LQCD_ERR_DEVICE;
@@ -449,6 +449,8 @@ lqcd_status lqcd_context_create(lqcd_context **out) {
     return set_error(nullptr, s, "context allocation failed");
   }
   ctx->red_partials_count = 1024 * kMaxRed;
+  ctx->cg_ring = reinterpret_cast<CgRing *>(ctx->red_host + kMaxRed);
+  ctx->cg_ring_dev = reinterpret_cast<CgRing *>(ctx->red_host_dev + kMaxRed);
   *out = ctx;
   return LQCD_OK;
 }

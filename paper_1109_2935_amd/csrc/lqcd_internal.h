@@ -11,6 +11,17 @@
 #include "lqcd.h"
 #include "lqcd_device.h"
 
+namespace lqcd {
+// One iteration of the device-driven CG as the host sees it; `iter` is written
+// last (iteration number, from 1).
+struct CgRing {
+  double rr, pp;
+  unsigned long long iter;
+  unsigned long long pad;
+};
+constexpr int kCgRing = 8;
+}  // namespace lqcd
+
 struct lqcd_context {
   int device = 0;
   std::string last_error;
@@ -20,6 +31,10 @@ struct lqcd_context {
   size_t red_partials_count = 0;
   double *red_host = nullptr;
   double *red_host_dev = nullptr;
+  // per-iteration values of the device-driven CG (kCgRing entries, pinned host
+  // memory after the reductions' result)
+  lqcd::CgRing *cg_ring = nullptr;
+  lqcd::CgRing *cg_ring_dev = nullptr;
   // general scratch vectors, grown on demand and reused between calls
   std::vector<void *> scratch;
   std::vector<size_t> scratch_bytes;
@@ -96,6 +111,23 @@ hipError_t launch_wilson(const WilsonLaunch &w, hipStream_t st);
 // for bit; block_threads is not used.
 bool wilson_split_fits(const WilsonLaunch &w);
 hipError_t launch_wilson_split(const WilsonLaunch &w, hipStream_t st);
+
+// CGNE iterations driven from the device (FP64, split form): the second launch
+// of each Schur application ends with the vector updates, whose coefficients
+// every workgroup forms from the previous launches' partial sums.
+struct CgStep {
+  double *x, *r, *p;        // even spinors: x += a p, r -= a q; p = t + b p
+  double *rr[2], *pp[2];    // partial sums of |r|^2 and |p|^2, one per workgroup; iteration k writes [k % 2]
+  double stop;              // |r|^2 at which updates end
+  unsigned long long iter;  // this iteration (from 1)
+  CgRing *ring;             // device address
+};
+bool cg_device_fits(const OpInfo &info);
+int cg_device_groups(const OpInfo &info);
+// sums set to the values before iteration 1
+hipError_t launch_cg_start(const OpInfo &info, const CgStep &c, double rr, double pp, hipStream_t st);
+// one iteration; tmp: odd spinor
+hipError_t launch_cg_iteration(const OpInfo &info, const CgStep &c, void *tmp, hipStream_t st);
 
 // Persistent multi-operator hopping term (mode W_HOP, coef 1).
 struct BatchJob {

@@ -383,6 +383,61 @@ struct CgOps {
   }
 };
 
+// CGNE iterations driven from the device (cg_device_fits): from |r|^2 = rr and
+// |p|^2 = pp, up to `most` iterations, until |r|^2 <= stop (p is then the last
+// iteration's) or a breakdown. Iterations are enqueued ahead of the values the
+// host sees, which the device writes to pinned memory; those enqueued past the
+// end leave x, r and p as they are. done: iterations taken; rr, pp: the last
+// values of |r|^2 before the last iteration and of |p|^2; rr_new: |r|^2 after it.
+struct CgAhead {
+  int done = 0;
+  bool breakdown = false;
+  double rr, pp, rr_new;
+};
+template <typename Seen>
+lqcd_status cg_ahead(Solver &S, const OpInfo &op, CgStep c, void *tmp, int most, CgAhead *st, Seen &&seen) {
+  lqcd_context *ctx = S.ctx;
+  const int n = cg_device_groups(op);
+  for (int k = 0; k < 2; ++k) {
+    c.rr[k] = ctx->red_partials + k * n;
+    c.pp[k] = ctx->red_partials + (2 + k) * n;
+  }
+  c.ring = ctx->cg_ring_dev;
+  for (int k = 0; k < kCgRing; ++k) __atomic_store_n(&ctx->cg_ring[k].iter, 0ull, __ATOMIC_RELEASE);
+  TRY(S.hip(launch_cg_start(op, c, st->rr, st->pp, S.st), "cg start"));
+  st->rr_new = st->rr;
+  int queued = 0;
+  lqcd_status status = LQCD_OK;
+  while (st->done < most) {
+    // two iterations ahead: one runs while the next is enqueued
+    while (queued < most && queued < st->done + 2) {
+      c.iter = ++queued;
+      TRY(S.hip(launch_cg_iteration(op, c, tmp, S.st), "cg iteration"));
+    }
+    const unsigned long long want = st->done + 1;
+    CgRing *e = ctx->cg_ring + want % kCgRing;
+    for (int spins = 1; __atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want; ++spins) {
+      if (spins % 1024) continue;
+      const hipError_t q = hipStreamQuery(S.st);
+      if (q == hipErrorNotReady) continue;
+      status = S.hip(q, "cg iteration");  // the stream has drained (or failed)
+      if (status == LQCD_OK && __atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want)
+        status = set_error(ctx, LQCD_ERR_DEVICE, "cg iteration did not report");
+      if (status != LQCD_OK) return status;
+    }
+    if (!(e->pp > 0)) {
+      st->breakdown = true;
+      break;
+    }
+    st->rr = st->rr_new;
+    st->rr_new = e->rr;
+    ++st->done;
+    seen(st->rr_new, st->rr / e->pp);
+    if (!(st->rr_new > c.stop)) break;
+  }
+  return S.hip(hipStreamSynchronize(S.st), "cg iteration");
+}
+
 // CG or CGNE (the same recurrences as lqcd_cg_solve) on nrhs systems at once:
 // every operator application is one launch over all sources, while each
 // system keeps its own scalars, its own reliable-update scale and its own stop
@@ -696,33 +751,59 @@ extern "C" lqcd_status lqcd_cg_solve(lqcd_context *ctx, const lqcd_operator *op_
   bool converged = rr_true <= stop;
   lqcd_status status = LQCD_OK;
   int it = 0;
+  // small lattices in one precision: iterations without a host round trip each
+  const bool ahead = cgne && !mixed && !recording && cg_device_fits(lo);
+  auto report = [&](double rr_true_now, double a) {
+    if (inf.history_len < prm->res_history_max) prm->res_history[inf.history_len++] = std::sqrt(rr_true_now);
+    if (verbose()) fprintf(stderr, "cg it %d |r|/|b| %.3e alpha %.3e\n", it, std::sqrt(rr_true_now) / bn, a);
+  };
   while (!converged && it < prm->max_iter) {
-    double a;
-    if (mid) {
-      TRY(S.hip(blas_convert(vp, p, lo.prec, p16, n, 1.0, S.st), "convert"));
-      TRY(A.apply(lo, q16, p16, 0, tmp_lo));
-      TRY(S.hip(blas_convert(lo.prec, q16, vp, q, n, 1.0, S.st), "convert"));
+    double a, rr_new, rr_new_true;
+    if (ahead) {
+      CgAhead run;
+      run.rr = rr;
+      run.pp = pp;
+      TRY(cg_ahead(S, lo, CgStep{(double *)xs, (double *)rs, (double *)p, {}, {}, stop, 0, nullptr}, tmp_lo,
+                   prm->max_iter - it, &run, [&](double v, double alpha) {
+                     ++it;
+                     report(v, alpha);
+                   }));
+      rr_new = rr_new_true = run.rr_new;
+      inf.matvecs += 2 * run.done;
+      // a residual that is not a number makes the next |p|^2 one
+      if (run.breakdown || !(rr_new == rr_new)) {
+        inf.matvecs++;
+        status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CGNE breakdown: |p| = 0");
+        break;
+      }
+      if (rr_new > stop) break;  // max_iter
+      inf.matvecs--;  // (the last search direction was not formed)
+      rr = run.rr;
     } else {
-      TRY(A.apply(lo, q, p, 0, tmp_lo));
+      if (mid) {
+        TRY(S.hip(blas_convert(vp, p, lo.prec, p16, n, 1.0, S.st), "convert"));
+        TRY(A.apply(lo, q16, p16, 0, tmp_lo));
+        TRY(S.hip(blas_convert(lo.prec, q16, vp, q, n, 1.0, S.st), "convert"));
+      } else {
+        TRY(A.apply(lo, q, p, 0, tmp_lo));
+      }
+      inf.matvecs++;
+      if (cgne) {
+        if (!(pp > 0)) { status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CGNE breakdown: |p| = 0"); break; }
+        a = rr / pp;
+      } else {
+        double d[2];
+        TRY(S.hip(blas_cdot(vp, p, q, n, red, S.st), "dot"));
+        TRY(S.result(2, d));
+        if (!(d[0] > 0)) { status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CG breakdown: <p, A p> <= 0"); break; }
+        a = rr / d[0];
+      }
+      TRY(S.hip(blas_cg_update(vp, xs, p, vp, rs, q, n, a, red, S.st), "cg update"));
+      TRY(S.result(1, &rr_new));
+      ++it;
+      rr_new_true = rr_new / (sc * sc);
+      report(rr_new_true, a);
     }
-    inf.matvecs++;
-    if (cgne) {
-      if (!(pp > 0)) { status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CGNE breakdown: |p| = 0"); break; }
-      a = rr / pp;
-    } else {
-      double d[2];
-      TRY(S.hip(blas_cdot(vp, p, q, n, red, S.st), "dot"));
-      TRY(S.result(2, d));
-      if (!(d[0] > 0)) { status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CG breakdown: <p, A p> <= 0"); break; }
-      a = rr / d[0];
-    }
-    double rr_new;
-    TRY(S.hip(blas_cg_update(vp, xs, p, vp, rs, q, n, a, red, S.st), "cg update"));
-    TRY(S.result(1, &rr_new));
-    ++it;
-    double rr_new_true = rr_new / (sc * sc);
-    if (inf.history_len < prm->res_history_max) prm->res_history[inf.history_len++] = std::sqrt(rr_new_true);
-    if (verbose()) fprintf(stderr, "cg it %d |r|/|b| %.3e alpha %.3e\n", it, std::sqrt(rr_new_true) / bn, a);
     if (recording && it % prm->record_every == 0 && *prm->record_count < prm->record_max) {
       // pure precision: x_k = x_e + xs, r_k = rs; e_k = x* - x_k
       const int j = *prm->record_count;

@@ -89,8 +89,21 @@ __device__ __forceinline__ cpx<R> clover_row_mul(const CloverRow<R> &r, int i, c
   return y;
 }
 
-template <typename S, typename R, int RECON, int MODE>
-__global__ void __launch_bounds__(kSplitThreads) wilson_split_kernel(WArgs<S> a) {
+// Sum of the n partials of a device-driven CG step, the same in every thread.
+__device__ __forceinline__ double cg_total(const double *part, int n) {
+  double t = 0;
+  for (int j = threadIdx.x & 63; j < n; j += 64) t += part[j];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  return t;
+}
+
+// CG: 0 none; 1: q = the result; x += a p, r -= a q (p the input xin, q not
+// stored); 2: p = the result + b p.
+enum { kCgNone = 0, kCgUpdate = 1, kCgDirection = 2 };
+
+template <typename S, typename R, int RECON, int MODE, int CG = kCgNone>
+__global__ void __launch_bounds__(kSplitThreads) wilson_split_kernel(WArgs<S> a, CgStep cg) {
   constexpr bool CLOV = MODE == W_HOP_CLOV || MODE == W_XPAY_CLOV, XPAY = MODE == W_XPAY_CLOV || MODE == W_XPAY;
   __shared__ R half[8 * 12 * kSplitPoints];
   __shared__ R full[MODE == W_HOP_CLOV ? 24 * kSplitPoints : 1];
@@ -185,6 +198,65 @@ __global__ void __launch_bounds__(kSplitThreads) wilson_split_kernel(WArgs<S> a)
           res[e] = scale_add(coef, acc[e], xv[e]);
       }
   }
+  if constexpr (CG != kCgNone) {
+    // Every wave forms the totals of the earlier launches (fixed order); the
+    // updates end, leaving x, r and p as they are, once |r|^2 <= stop or |p|^2
+    // is not positive.
+    const int n = gridDim.x, b0 = (cg.iter & 1) ^ 1, b1 = cg.iter & 1;
+    const double rr = cg_total(cg.rr[b0], n), pp = cg_total(cg.pp[b0], n);
+    double *now = CG == kCgUpdate ? cg.rr[b1] : cg.pp[b1];
+    double own = 0;
+    auto chunk = [&](double *f) { return reinterpret_cast<Chunk<double, 4> *>(f + ((int64_t)w * vs + v) * 4); };
+    const double q[4] = {res[0].re, res[0].im, res[1].re, res[1].im};
+    if constexpr (CG == kCgUpdate) {
+      const bool go = rr > cg.stop && pp > 0;
+      if (epi && go) {
+        const double f = rr / pp;
+        Chunk<double, 4> x = *chunk(cg.x), r = *chunk(cg.r);
+        const Chunk<double, 4> p = *chunk(cg.p);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          x.v[k] += f * p.v[k];
+          r.v[k] -= f * q[k];
+          own += r.v[k] * r.v[k];
+        }
+        *chunk(cg.x) = x;
+        *chunk(cg.r) = r;
+      }
+      if (!go && threadIdx.x == 0 && blockIdx.x == 0) own = rr;
+    } else {
+      const double next = cg_total(cg.rr[b1], n);
+      const bool go = next > cg.stop && pp > 0;
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        CgRing *e = cg.ring + cg.iter % kCgRing;
+        e->rr = next;
+        e->pp = pp;
+        __hip_atomic_store(&e->iter, cg.iter, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+      if (epi && go) {
+        const double f = next / rr;
+        Chunk<double, 4> p = *chunk(cg.p);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          p.v[k] = q[k] + f * p.v[k];
+          own += p.v[k] * p.v[k];
+        }
+        *chunk(cg.p) = p;
+      }
+      if (!go && threadIdx.x == 0 && blockIdx.x == 0) own = pp;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) own += __shfl_xor(own, off, 64);
+    __shared__ double waves[kSplitThreads / 64];
+    if (lane == 0) waves[w] = own;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0;
+      for (int j = 0; j < kSplitThreads / 64; ++j) t += waves[j];
+      now[blockIdx.x] = t;
+    }
+    return;
+  }
   if (!epi) return;
   Chunk<S, 4> o;
 #pragma unroll
@@ -226,13 +298,17 @@ template <int P, int RECON> static hipError_t launch_split2(const WilsonLaunch &
   a.rg = rhs_group(w.nrhs);
   const dim3 grid(rhs_grid(w.g.Vh, w.nrhs, kSplitPoints)), block(kSplitThreads);
   switch (w.mode) {
-    case W_HOP: hipLaunchKernelGGL((wilson_split_kernel<S, R, RECON, W_HOP>), grid, block, 0, st, a); break;
-    case W_HOP_CLOV: hipLaunchKernelGGL((wilson_split_kernel<S, R, RECON, W_HOP_CLOV>), grid, block, 0, st, a); break;
-    case W_XPAY_CLOV: hipLaunchKernelGGL((wilson_split_kernel<S, R, RECON, W_XPAY_CLOV>), grid, block, 0, st, a); break;
-    case W_XPAY: hipLaunchKernelGGL((wilson_split_kernel<S, R, RECON, W_XPAY>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
+#define CASE(M)                                                                                       \
+  case M:                                                                                             \
+    hipLaunchKernelGGL((wilson_split_kernel<S, R, RECON, M>), grid, block, 0, st, a, CgStep{});       \
+    return hipGetLastError();
+    CASE(W_HOP)
+    CASE(W_HOP_CLOV)
+    CASE(W_XPAY_CLOV)
+    CASE(W_XPAY)
+#undef CASE
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int P> static hipError_t launch_split1(const WilsonLaunch &w, hipStream_t st) {
@@ -249,6 +325,70 @@ hipError_t launch_wilson_split(const WilsonLaunch &w, hipStream_t st) {
   switch (w.prec) {
     case LQCD_F64: return launch_split1<LQCD_F64>(w, st);
     case LQCD_F32: return launch_split1<LQCD_F32>(w, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------------
+// CGNE iterations without a host round trip: the recurrences of lqcd_cg_solve on
+// Mhat in FP64, for lattices that take the split form. An iteration is the four
+// launches of the two Schur applications; a lattice of 2048 sites took eight and
+// two stream synchronisations (62 us an iteration, 30 us of them kernels).
+
+bool cg_device_fits(const OpInfo &info) {
+  return info.prec == LQCD_F64 && info.op->action == LQCD_WILSON_CLOVER && (int64_t)info.vh <= kSplitMost;
+}
+int cg_device_groups(const OpInfo &info) { return rhs_grid((int)info.vh, 1, kSplitPoints); }
+
+__global__ void __launch_bounds__(256) cg_start_kernel(CgStep c, int n, double rr, double pp) {
+  for (int j = threadIdx.x; j < n; j += 256) {
+    c.rr[0][j] = j == 0 ? rr : 0;
+    c.pp[0][j] = j == 0 ? pp : 0;
+  }
+}
+
+hipError_t launch_cg_start(const OpInfo &info, const CgStep &c, double rr, double pp, hipStream_t st) {
+  hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(256), 0, st, c, cg_device_groups(info), rr, pp);
+  return hipGetLastError();
+}
+
+template <int RECON> static hipError_t cg_iteration(const OpInfo &info, const CgStep &c, void *tmp, hipStream_t st) {
+  const lqcd_operator *op = info.op;
+  WArgs<double> a;
+  a.g = info.g;
+  a.gauge = (const double *)op->gauge;
+  a.partials = nullptr;
+  a.nrhs = a.rg = 1;
+  const dim3 grid(cg_device_groups(info)), block(kSplitThreads);
+  for (int dagger = 0; dagger < 2; ++dagger) {
+    const double *in = dagger ? c.r : c.p;
+    a.dagger = dagger;
+    a.out = (double *)tmp;
+    a.in = in;
+    a.xin = nullptr;
+    a.clov = (const double *)op->clover_inv + info.vh * 72;  // odd sites
+    a.parity = 1;
+    a.coef = 1.0;
+    hipLaunchKernelGGL((wilson_split_kernel<double, double, RECON, W_HOP_CLOV>), grid, block, 0, st, a, CgStep{});
+    a.out = nullptr;
+    a.in = (const double *)tmp;
+    a.xin = in;
+    a.clov = (const double *)op->clover;  // even sites
+    a.parity = 0;
+    a.coef = -op->kappa * op->kappa;
+    if (dagger)
+      hipLaunchKernelGGL((wilson_split_kernel<double, double, RECON, W_XPAY_CLOV, kCgDirection>), grid, block, 0, st, a, c);
+    else
+      hipLaunchKernelGGL((wilson_split_kernel<double, double, RECON, W_XPAY_CLOV, kCgUpdate>), grid, block, 0, st, a, c);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_iteration(const OpInfo &info, const CgStep &c, void *tmp, hipStream_t st) {
+  switch (info.recon) {
+    case 18: return cg_iteration<18>(info, c, tmp, st);
+    case 12: return cg_iteration<12>(info, c, tmp, st);
+    case 8: return cg_iteration<8>(info, c, tmp, st);
   }
   return hipErrorInvalidValue;
 }

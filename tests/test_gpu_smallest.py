@@ -68,3 +68,36 @@ def test_staggered_cg_2x2x2x2_against_dense_lu(ctx):
     assert st == L.LQCD_OK, L.lqcd_last_error(ctx)
     xs = np_of(o.export_spinor(x, 0)).reshape(-1)[idx]
     assert rel(xs, ref) < 1e-8
+
+
+# CGNE in one precision on at most 16384 even sites iterates without a host round
+# trip; a solve that records its iterates takes the host's loop. Both run the
+# same recurrences (sums in another order): less than one workgroup, a workgroup
+# that is not full, several, the largest size, and the first beyond it.
+@pytest.mark.parametrize("dims,recon", [((2, 2, 2, 2), 18), ((6, 2, 6, 2), 12), ((8, 4, 6, 8), 8), ((16, 16, 8, 16), 18),
+                                        ((16, 16, 8, 18), 18)])
+@pytest.mark.parametrize("max_iter", [1, 3, 1000])
+def test_cgne_device_iterations_equal_host_loop(ctx, dims, recon, max_iter):
+    import ctypes
+    U = synth.gauge_field(dims, 0.25, 131)
+    o = ops.wilson_clover(ctx, U, dims, 0.12, 1.0, 0, recon)
+    b = o.import_spinor(synth.gaussian_spinor(dims, 132), -1)
+    runs = []
+    for record in (False, True):
+        prm = ops.cg_params(1e-10, max_iter, history=1000)
+        if record:
+            rec, err, zero = o.spinor(nrhs=1), o.spinor(nrhs=1), o.spinor()
+            count = ctypes.c_int32(0)
+            prm.record_r, prm.record_e, prm.record_xstar = rec.data_ptr(), err.data_ptr(), zero.data_ptr()
+            prm.record_every, prm.record_max, prm.record_count = 1000, 1, ctypes.pointer(count)
+        x = o.spinor(full=True)
+        st, info = L.lqcd_cg_solve(ctx, o.op, None, prm, x, b)
+        runs.append((st, info.iters, info.restarts, info.matvecs, ops.residual_history(prm, info),
+                     np_of(o.export_spinor(x, -1))))
+    dev, host = runs
+    assert dev[:4] == host[:4]
+    assert dev[0] == (L.LQCD_OK if max_iter == 1000 else L.LQCD_ERR_NOT_CONVERGED)
+    assert len(dev[4]) == dev[1] == len(host[4])
+    # FP64 sums in another order: the recurrences amplify 1e-16 by the steps taken
+    assert np.allclose(dev[4], host[4], rtol=1e-9)
+    assert rel(dev[5], host[5]) < 1e-11
