@@ -52,13 +52,18 @@ inline size_t ptc_adj_frag_bytes(const PtcLayerDev &L) { return (size_t)L.madj_t
 
 // neighbour table of the 8 hop paths, 2 * 8 * Vh ints (see ptc_nbr_kernel)
 hipError_t launch_ptc_nbr(const Geom &g, int *tab, hipStream_t st);
-// variant: 10 x sites per workgroup + waves per SIMD hint: 642 or 322
+// link table of the hop paths for the 16-input-channel form (ptc_link_kernel)
+inline size_t ptc_link_bytes(size_t vh) { return 2 * 8 * vh * 36; }
+hipError_t launch_ptc_links(const PtcGeo &q, const int *nbr, void *tab, hipStream_t st);
+// variant: the general form with 64 or 32 sites per workgroup (642, 322), or the
+// form for 16 input channels (which needs `links`)
+constexpr int kPtcForward16 = 16;
 // in: BF16 activations; out: BF16 activations, or (out_f32, one channel) an FP32 packed spinor
 // par: output parity, or -1 for both in one launch (workgroups of the two
 // parities interleaved); zero_par: parity on which the input is known to
 // vanish (-1: none)
-hipError_t launch_ptc_forward(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *in, void *out,
-                              int out_f32, int par, int variant, int zero_par, hipStream_t st);
+hipError_t launch_ptc_forward(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *links, const void *in,
+                              void *out, int out_f32, int par, int variant, int zero_par, hipStream_t st);
 // layer-0 activations from an FP32 packed even field
 hipError_t launch_ptc_input(int64_t vh, const void *in_even, void *act, hipStream_t st);
 // the output cotangent (FP32 packed even spinor) as the BF16 delta of the last layer

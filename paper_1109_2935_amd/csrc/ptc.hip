@@ -7,18 +7,18 @@
 // no such network; it is used as a learned preconditioner of flexible GCR
 // (Section III-B: the outer solver must be flexible).
 //
-// Activations between layers are BF16, channel-interleaved per site (packed
-// index site * C + channel) in 16-byte chunks of 8 reals, chunk-major within
-// each parity block (act_load / act_store); the network output is an FP32
-// packed spinor. The channel mixing is a complex GEMM
+// Activations between layers are BF16, one record of 24 reals (48 bytes, in the
+// order spin, colour, re/im) per packed index site * C + channel of a parity
+// block; the network output is an FP32 packed spinor. The channel mixing is a complex GEMM
 //   O[(o,s)][(c,x)] = sum_{(i,p,s')} W[(o,s)][(i,p,s')] Y[(i,p,s')][(c,x)],
 // Y = T_p psi_i, run on the BF16 matrix cores (v_mfma_f32_16x16x32_bf16, FP32
 // accumulation) in real form with interleaved real/imaginary rows:
 //   A[2m+r][2k+r'] = [[Wr, -Wi],[Wi, Wr]][r][r'],  B[2k+r'][n] = (Yr, Yi)[r'].
-// A workgroup owns a tile of 16 sites of one parity: it builds Y for a chunk of
-// input channels in LDS (parallel transport, converted to BF16), then each of
-// its 4 waves runs the MFMA tiles it owns; weights come pre-packed in the
-// per-lane A-operand order, so each A fragment is one coalesced 16-byte load.
+// General form: a workgroup owns 64 or 32 sites of one parity; it builds Y for a
+// chunk of input channels in LDS (parallel transport, converted to BF16), then
+// each of its 4 waves runs the MFMA tiles it owns. Layers from 16 channels keep Y
+// in registers (ptc_forward16_kernel). Weights come pre-packed in the per-lane
+// A-operand order, so each A fragment is one coalesced 16-byte load.
 #include <algorithm>
 #include <type_traits>
 
@@ -42,9 +42,25 @@ constexpr int kTile = 16;      // sites per workgroup tile
 constexpr int kPtcThreads = 256;
 constexpr int kLdsPad = 8;     // bf16 padding per LDS row (bank spread)
 
-// activation access: 24 reals of packed index idx in a parity block of vs entries
-__device__ __forceinline__ void act_load(const bf16 *__restrict__ blk, int64_t vs, int64_t idx, float *r) {
-  load_chunks<bf16, 24, 8, float>(blk, vs, idx, r);
+// activation access: the 24 reals (48 bytes) of packed index idx in a parity block
+__device__ __forceinline__ void act_load(const bf16 *__restrict__ blk, int64_t idx, float *r) {
+  load_chunks<bf16, 24, 8, float>(blk + idx * 24, 1, 0, r);
+}
+
+// An FP32 link from 12 or 18 stored reals.
+template <int RC> __device__ __forceinline__ Link<float> ptc_link(const float *v) {
+  Link<float> u = unpack_link<RC == 12 ? 12 : 18, float>(v);
+  if constexpr (RC == 12) {
+    // conj(row 0 x row 1), its sums in the order that the activations' roundings have had
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int k = (j + 1) % 3, l = (j + 2) % 3;
+      const cpx<float> a = u.m[0][k], b = u.m[1][l], c = u.m[0][l], d = u.m[1][k];
+      u.m[2][j] = mk<float>((a.re * b.re - a.im * b.im) - (c.re * d.re - c.im * d.im),
+                            -((a.re * b.im + a.im * b.re) - (c.re * d.im + c.im * d.re)));
+    }
+  }
+  return u;
 }
 
 __device__ __forceinline__ f32x4_t mfma_bf16(const bf16x8_t &a, const bf16x8_t &b, const f32x4_t &c) {
@@ -93,7 +109,7 @@ __device__ __forceinline__ void transportn_lds(const PtcGeo &q, const int *__res
   const bf16 *blk = act + (int64_t)(p == 0 ? par : 1 - par) * vs * 24;
   float r[NCH][24];
 #pragma unroll
-  for (int k = 0; k < NCH; ++k) act_load(blk, vs, (int64_t)n * C + i0 + k * kstep, r[k]);
+  for (int k = 0; k < NCH; ++k) act_load(blk, (int64_t)n * C + i0 + k * kstep, r[k]);
   if (p != 0) {
     const int mu = (p - 1) >> 1;
     const bool fwd = ((p - 1) & 1) == 0;
@@ -101,7 +117,7 @@ __device__ __forceinline__ void transportn_lds(const PtcGeo &q, const int *__res
     // forward: U_mu(x) at x; backward: U_mu(x - mu)^+ at the neighbour
     load_site<float, RECON, float>(q.gauge + (int64_t)(2 * mu + (fwd ? par : 1 - par)) * vh * RECON, vh, fwd ? s : n,
                                    lv);
-    const Link<float> U0 = unpack_link<RECON, float>(lv);
+    const Link<float> U0 = ptc_link<RECON>(lv);
     // the matrix applied: U, or U^+ for a backward hop (selected once), times the boundary sign
     Link<float> U;
 #pragma unroll
@@ -159,25 +175,14 @@ __device__ __forceinline__ bf16x8_t lds_frag(const __bf16 *row) {
 
 constexpr int kFwRow = 16 * 8 + kLdsPad;  // bf16 per LDS row: 16 items x 8 K values + padding
 
-// PIPE: 0 generic; 1 and 2 the pipelined 16-channel form with the colour
-// products on BF16 dot2 (1) or on 4x4x4 matrix-core blocks (2); 3 and 4 the
-// same split between waves: the first half of the waves transport path p + 1
-// into one LDS buffer while the second half multiply path p from the other
-// (one barrier per path, so the vector and matrix work of a workgroup overlap).
-// NTH threads (NTH / 64 waves) per workgroup; RC the link format (12 or 18
-// reals) of the pipelined forms.
-template <int NS, int WPE, int PIPE, int NTH = kPtcThreads, int RC = 18>
-__global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WPE)))
+template <int NS>
+__global__ void __launch_bounds__(kPtcThreads) __attribute__((amdgpu_waves_per_eu(2)))
 ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void *out, int out_f32, int par_arg,
                    int zero_par) {
   constexpr int kFwSites = NS, NT = 3 * NS / 16;
-  constexpr bool SPLIT = PIPE >= 3;
-  constexpr int TRANS = (PIPE == 2 || PIPE == 4) ? 2 : 1;  // colour products: 1 dot2, 2 matrix cores
-  constexpr int NW = NTH / 64;                // waves
-  constexpr int NWC = SPLIT ? NW / 2 : NW;    // waves doing the matrix products
+  constexpr int NWC = kPtcThreads / 64;       // waves
   constexpr int JM = (8 + NWC - 1) / NWC;     // m-tiles per wave at most (8 m-tiles for 16 output channels)
-  constexpr int kBuf = 3 * NS * kFwRow;       // bf16 per LDS buffer of transported inputs
-  __shared__ __align__(16) __bf16 Bt[(SPLIT ? 2 : 1) * kBuf];
+  __shared__ __align__(16) __bf16 Bt[3 * NS * kFwRow];
   // each XCD takes a contiguous range of site tiles, so that the neighbours'
   // activations are read from its own L2; with par_arg < 0 both output
   // parities are computed, workgroups 2t and 2t + 1 taking tile t of the even
@@ -188,22 +193,18 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
   if (par_arg < 0) wl >>= 1;
   const int s0 = wl * kFwSites;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool producer = SPLIT && wave < NW / 2;  // (split forms) transports only
-  const int cw = SPLIT ? wave - NW / 2 : wave;   // index among the waves doing products
   // this wave's output tiles
-  int mbase = 0, nm = 0, nbase = 0, nn = 0;
-  if (producer) {
-  } else if (L.mtiles >= NWC) {
-    mbase = cw;
-    nm = (L.mtiles - cw + NWC - 1) / NWC;
-    nbase = 0;
+  int mbase, nm, nbase = 0, nn;
+  if (L.mtiles >= NWC) {
+    mbase = wave;
+    nm = (L.mtiles - wave + NWC - 1) / NWC;
     nn = NT;
   } else {
     const int split = NWC / L.mtiles;  // waves per m-tile
-    mbase = cw % L.mtiles;
+    mbase = wave % L.mtiles;
     nm = 1;
     nn = (NT + split - 1) / split;
-    nbase = (cw / L.mtiles) * nn;
+    nbase = (wave / L.mtiles) * nn;
     nn = max(0, min(nn, NT - nbase));
   }
   f32x4_t acc[JM][NT];
@@ -229,25 +230,6 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
             if (j < nm) ac[j][t] = mfma_bf16(a[j], b, ac[j][t]);
         }
       }
-    }
-  };
-  // the same product with compile-time tile counts (all loads of a K step
-  // issued before its MFMAs, no per-tile branches): SM m-tiles x SN n-tiles
-  auto mma_static = [&](auto smc, auto snc, auto &ac, const __bf16 *Bb, int q0) {
-    constexpr int SM = decltype(smc)::value, SN = decltype(snc)::value;
-#pragma unroll
-    for (int kl = 0; kl < 4; ++kl) {
-      const int ks = q0 / 4 + kl;
-      bf16x8_t a[SM], b[SN];
-#pragma unroll
-      for (int j = 0; j < SM; ++j) a[j] = A[((size_t)(mbase + NWC * j) * L.fw_ks + ks) * 64 + lane];
-#pragma unroll
-      for (int t = 0; t < SN; ++t)
-        b[t] = lds_frag(Bb + ((nbase + t) * 16 + (lane & 15)) * kFwRow + kl * 32 + 8 * (lane >> 4));
-#pragma unroll
-      for (int t = 0; t < SN; ++t)
-#pragma unroll
-        for (int j = 0; j < SM; ++j) ac[j][t] = mfma_bf16(a[j], b[t], ac[j][t]);
     }
   };
   // Output. Row m = 16 mt + 4 g + jj (g = lane / 16) of a tile is channel
@@ -288,19 +270,19 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
     const int per_chunk = kFwSites * L.cout;
     if (!out_f32) {
       bf16 *blk = (bf16 *)out + (int64_t)par * vs * 24;
-      for (int w = threadIdx.x; w < 3 * per_chunk; w += NTH) {
+      for (int w = threadIdx.x; w < 3 * per_chunk; w += kPtcThreads) {
         const int k = w / per_chunk, rem = w - k * per_chunk;
         const int sl = rem / L.cout, o = rem - sl * L.cout;
         const int s = s0 + sl;
         if (s < q.g.Vh)
-          *reinterpret_cast<uint4 *>(blk + ((int64_t)k * vs + (int64_t)s * L.cout + o) * 8) =
+          *reinterpret_cast<uint4 *>(blk + ((int64_t)s * L.cout + o) * 24 + 8 * k) =
               *reinterpret_cast<const uint4 *>(Bt + sl * srow + o * 24 + 8 * k);
       }
     } else {
       // FP32 packed spinor (chunks of 4 reals); the network's last layer (one channel)
       const float *Sf = reinterpret_cast<const float *>(Bt);
       float *blk = (float *)out + (int64_t)par * vs * 24;
-      for (int w = threadIdx.x; w < 6 * per_chunk; w += NTH) {
+      for (int w = threadIdx.x; w < 6 * per_chunk; w += kPtcThreads) {
         const int k = w / per_chunk, rem = w - k * per_chunk;
         const int sl = rem / L.cout, o = rem - sl * L.cout;
         const int s = s0 + sl;
@@ -310,200 +292,6 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
       }
     }
   };
-  if constexpr (PIPE != 0) {
-    // 16 input channels: TPS threads per site, thread un taking channels
-    // un + TPS k (k < KC); one path per chunk; the loads of path p + 1 are
-    // issued before the matrix products of path p, so their latency overlaps them.
-    constexpr int TPS = (SPLIT ? NTH / 2 : NTH) / kFwSites, KC = 16 / TPS;
-    static_assert(TPS * KC == 16 && (TPS == 8 || TPS == 16), "pipelined path: 8 or 16 threads per site");
-    __shared__ int nbL[kFwSites][8];
-    // (in the split forms the transporting threads are 0 .. NTH / 2 - 1)
-    const int un = threadIdx.x % TPS, sl = (threadIdx.x / TPS) % kFwSites, s = s0 + sl;
-    const bool valid = s < q.g.Vh;
-    const int64_t vh = q.g.Vh, vs = vh * 16;
-    if (un < 8 && (!SPLIT || producer)) nbL[sl][un] = valid ? nbr[((int64_t)par * 8 + un) * vh + s] : 0;
-    __syncthreads();
-    // activation words and link reals of the path in flight
-    static_assert(RC == 12 || RC == 18, "link format");
-    uint4 rawA[KC][3];
-    float lvA[RC] = {};
-    // (always inlined: the register sets are passed by reference and must not
-    // go to memory)
-    auto issue = [&](uint4 (&raw)[KC][3], float (&lv)[RC], int p) __attribute__((always_inline)) {
-      if (!valid) return;
-      const int n = p == 0 ? s : (nbL[sl][p - 1] & 0x7fffffff);
-      const bf16 *blk = in + (int64_t)(p == 0 ? par : 1 - par) * vs * 24;
-#pragma unroll
-      for (int k = 0; k < KC; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          raw[k][c] = *reinterpret_cast<const uint4 *>(blk + ((int64_t)c * vs + (int64_t)n * 16 + un + TPS * k) * 8);
-      if (p != 0) {
-        const int mu = (p - 1) >> 1;
-        const bool fwd = ((p - 1) & 1) == 0;
-        const int lsite = fwd ? s : n, lpar = fwd ? par : 1 - par;
-        load_site<float, RC, float>(q.gauge + (int64_t)(2 * mu + lpar) * vh * RC, vh, lsite, lv);
-      }
-    };
-    auto compute = [&](__bf16 *Bb, const uint4 (&raw)[KC][3], const float (&lv)[RC], int p)
-                       __attribute__((always_inline)) {
-      __bf16 *dst = Bb + sl * kFwRow + 8 * un;
-      // (the matrix-core form keeps every lane in its products: a lane of a
-      // site beyond Vh multiplies zeros and stores zeros)
-      if (TRANS != 2 && !valid) {
-        const bf16x8_t zero = {};
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            *reinterpret_cast<bf16x8_t *>(dst + c * kFwSites * kFwRow + 8 * TPS * k) = zero;
-        return;
-      }
-      // word 3 sp + col of a channel: the (re, im) BF16 pair of spin sp, colour col
-      uint32_t w[KC][12];
-#pragma unroll
-      for (int k = 0; k < KC; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          w[k][4 * c + 0] = valid ? raw[k][c].x : 0u;
-          w[k][4 * c + 1] = valid ? raw[k][c].y : 0u;
-          w[k][4 * c + 2] = valid ? raw[k][c].z : 0u;
-          w[k][4 * c + 3] = valid ? raw[k][c].w : 0u;
-        }
-      if (p != 0) {
-        const bool fwd = ((p - 1) & 1) == 0;
-        const float ph = nbL[sl][p - 1] < 0 ? -1.f : 1.f;
-        const Link<float> U0 = unpack_link<RC, float>(lv);
-        if constexpr (TRANS == 2) {
-          // matrix cores: lanes 4b .. 4b+3 are one site (8 lanes per site), so
-          // a 4x4x4 block is one site's link times 4 of its (channel, spin)
-          // vectors; a vector's 3 words are its own B operand (K = c0 re, c0 im,
-          // c1 re, c1 im | c2 re, c2 im, 0, 0) and its D column is U v in FP32
-          Link<float> U;  // U, or U^+ for a backward hop, times the boundary sign
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-              const cpx<float> e = fwd ? U0.m[a][b] : conj(U0.m[b][a]);
-              U.m[a][b] = ph * e;
-            }
-          mf_s4 A4[2][2];
-          mf_link_rows<bf16, false>(U, lane & 3, A4);
-          const mf_f4 zero4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-              const mf_s4 b0 = __builtin_bit_cast(mf_s4, u32x2_t{w[k][3 * sp], w[k][3 * sp + 1]});
-              const mf_s4 b1 = __builtin_bit_cast(mf_s4, u32x2_t{w[k][3 * sp + 2], 0u});
-              mf_f4 d0 = Mf4<bf16>::mma(A4[0][0], b0, zero4);
-              d0 = Mf4<bf16>::mma(A4[0][1], b1, d0);
-              mf_f4 d1 = Mf4<bf16>::mma(A4[1][0], b0, zero4);
-              d1 = Mf4<bf16>::mma(A4[1][1], b1, d1);
-              w[k][3 * sp + 0] = __builtin_bit_cast(uint32_t, pack_bf16x2(d0[0], d0[1]));
-              w[k][3 * sp + 1] = __builtin_bit_cast(uint32_t, pack_bf16x2(d0[2], d0[3]));
-              w[k][3 * sp + 2] = __builtin_bit_cast(uint32_t, pack_bf16x2(d1[0], d1[1]));
-            }
-        } else {
-          // the applied matrix (U, or U^+ for a backward hop, times the boundary
-          // sign) as BF16 pairs: re(u v) = dot((Ur, -Ui), (vr, vi)),
-          // im(u v) = dot((Ui, Ur), (vr, vi)), products exact, FP32 sums
-          bf16x2_t Pr[3][3], Pi[3][3];
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-              const cpx<float> e = fwd ? U0.m[a][b] : conj(U0.m[b][a]);
-              Pr[a][b] = pack_bf16x2(ph * e.re, -ph * e.im);
-              Pi[a][b] = pack_bf16x2(ph * e.im, ph * e.re);
-            }
-#pragma unroll
-          for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int sp = 0; sp < 4; ++sp) {
-              bf16x2_t v[3];
-#pragma unroll
-              for (int b = 0; b < 3; ++b) v[b] = __builtin_bit_cast(bf16x2_t, w[k][3 * sp + b]);
-              uint32_t o[3];
-#pragma unroll
-              for (int a = 0; a < 3; ++a) {
-                float re = 0.f, im = 0.f;
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                  re = __builtin_amdgcn_fdot2_f32_bf16(Pr[a][b], v[b], re, false);
-                  im = __builtin_amdgcn_fdot2_f32_bf16(Pi[a][b], v[b], im, false);
-                }
-                o[a] = __builtin_bit_cast(uint32_t, pack_bf16x2(re, im));
-              }
-#pragma unroll
-              for (int a = 0; a < 3; ++a) w[k][3 * sp + a] = o[a];
-            }
-        }
-      }
-      // colour c: the four spins' (re, im) words
-#pragma unroll
-      for (int k = 0; k < KC; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          *reinterpret_cast<uint4 *>(dst + c * kFwSites * kFwRow + 8 * TPS * k) =
-              make_uint4(w[k][c], w[k][3 + c], w[k][6 + c], w[k][9 + c]);
-    };
-    // per path: transport into LDS, issue the next path's loads, then the
-    // matrix products (their latency overlaps the products)
-    constexpr int kSplitN = (NT + NWC - 1) / NWC;  // n-tiles per wave when one m-tile is split over all waves
-    const int form = (nm == JM && nn == NT) ? 2 : (nm == 1 && nn == kSplitN) ? 1 : (nn > 0 ? 0 : -1);
-    auto products = [&](auto &ac, const __bf16 *Bb, int p) {
-      if (form == 2)
-        mma_static(std::integral_constant<int, JM>(), std::integral_constant<int, NT>(), ac, Bb, 16 * p);
-      else if (form == 1)
-        mma_static(std::integral_constant<int, 1>(), std::integral_constant<int, kSplitN>(), ac, Bb, 16 * p);
-      else if (form == 0)
-        mma_chunk(ac, Bb, 16 * p, 16);
-    };
-    if constexpr (SPLIT) {
-      // iteration i: the transporting waves fill buffer i % 2 with path i while
-      // the others multiply path i - 1 from buffer (i - 1) % 2; the barrier
-      // ending iteration i publishes path i and frees buffer (i - 1) % 2. The
-      // accumulators live in the multiplying waves' branch only (they are not
-      // held while transporting), which also stages the output tile.
-      if (producer) {
-        issue(rawA, lvA, 0);
-#pragma unroll 1
-        for (int i = 0; i < 10; ++i) {
-          if (i < 9) {
-            compute(Bt + (i & 1) * kBuf, rawA, lvA, i);
-            if (i + 1 < 9) issue(rawA, lvA, i + 1);
-          }
-          __syncthreads();
-        }
-      } else {
-        f32x4_t cacc[JM][NT];
-#pragma unroll
-        for (int j = 0; j < JM; ++j)
-#pragma unroll
-          for (int t = 0; t < NT; ++t) cacc[j][t] = f32x4_t{0, 0, 0, 0};
-#pragma unroll 1
-        for (int i = 0; i < 10; ++i) {
-          if (i > 0) products(cacc, Bt + ((i - 1) & 1) * kBuf, i - 1);
-          __syncthreads();
-        }
-        stage(cacc);
-      }
-      __syncthreads();
-      store_out();
-      return;
-    } else {
-      issue(rawA, lvA, 0);
-#pragma unroll 1
-      for (int p = 0; p < 9; ++p) {
-        __syncthreads();
-        compute(Bt, rawA, lvA, p);
-        if (p + 1 < 9) issue(rawA, lvA, p + 1);
-        __syncthreads();
-        products(acc, Bt, p);
-      }
-    }
-  } else {
   // input known to vanish on parity zero_par (the network input lives on even
   // sites): the items reading that parity are zero, and when every hop is
   // zero only the identity items' K steps are multiplied
@@ -565,11 +353,260 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
     __syncthreads();
     mma_chunk(acc, Bt, q0, ipc);
   }
-  }
   __syncthreads();
   stage(acc);
   __syncthreads();
   store_out();
+}
+
+// ---------------------------------------------------------------------------
+// forward from 16 channels
+//
+// The colour products U v run on v_mfma_f32_4x4x4_16b_bf16 with the vectors as
+// the A operand and the link as the B operand: block (site, channel), row = spin
+// (its colour vector as stored), column j = row j of U in real form, once for
+// the real and once for the imaginary parts. Lane 16 kg + 4 s + j then holds the
+// four spins of (site s, channel kg, colour j), which, rounded to BF16, is its B
+// operand of the 16x16x32 channel product with column 4 s + j and K group kg:
+// the transported inputs never leave the registers. (Column 4 s + 3 is unused: a
+// quarter of the channel product is spent on it.) The links are read as BF16 rows
+// from a table made once per application, the activations as 12-byte rows of the
+// 48-byte records: four channels of a site are 192 bytes in a row.
+// A wave owns 8 sites and all output channels; the weights of a path (32 KB)
+// are staged in LDS for the workgroup's 64 sites, and the activations, links and
+// weights of path p + 1 are loaded while path p is multiplied, an eighth of them
+// at a time: issued together they hold up every wave of the SIMD until the last
+// is accepted (3.45 instead of 2.95 ms). Loads are unconditional and tile counts
+// compile-time, as in ptc_bwd_data_kernel. 16 sites per wave or loads two paths
+// ahead need more registers than two waves per SIMD have (4.1 and 3.9 ms).
+// Bound by the matrix cores and the loads together: at 32^3 x 64, 16 -> 16, 2.95 ms
+// for both parities, of which the products take 1.6 ms at the cores' peak and
+// a wave's 1 KB loads 34 cycles each; 16 -> 1, one parity: 0.80 ms. The form that
+// transported through LDS (producer and consumer waves) took 3.23 and 1.00 ms.
+// U is rounded to BF16, colour and channel sums are in FP32, and the transported
+// inputs are rounded to BF16, each sum in the order of that form.
+
+// Link table of the hop paths: entry [par][p - 1][s] holds the applied matrix (U,
+// or U^+ for a backward hop, times the boundary sign), 9 words (Re, -Im) in BF16.
+__global__ void __launch_bounds__(256) ptc_link_kernel(PtcGeo q, const int *__restrict__ nbr, uint32_t *__restrict__ tab) {
+  const int64_t vh = q.g.Vh;
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int par = blockIdx.y >> 3, p = blockIdx.y & 7, mu = p >> 1;
+  const bool fwd = (p & 1) == 0;
+  if (s >= vh) return;
+  const int e = nbr[((int64_t)par * 8 + p) * vh + s];
+  const int64_t ls = fwd ? s : (e & 0x7fffffff);
+  const float *base = q.gauge + (int64_t)(2 * mu + (fwd ? par : 1 - par)) * vh * q.recon;
+  Link<float> U0;
+  if (q.recon == 12) {
+    float lv[12];
+    load_site<float, 12, float>(base, vh, ls, lv);
+    U0 = ptc_link<12>(lv);
+  } else {
+    float lv[18];
+    load_site<float, 18, float>(base, vh, ls, lv);
+    U0 = ptc_link<18>(lv);
+  }
+  const float ph = e < 0 ? -1.f : 1.f;
+  uint32_t *o = tab + (((int64_t)par * 8 + p) * vh + s) * 9;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const cpx<float> m = fwd ? U0.m[a][b] : conj(U0.m[b][a]);
+      o[3 * a + b] = __builtin_bit_cast(uint32_t, pack_bf16x2(ph * m.re, -(ph * m.im)));
+    }
+}
+
+constexpr int kF16Sites = 64;
+constexpr int kF16Threads = 512;
+constexpr int kF16Waves = kF16Threads / 64;
+constexpr int kF16Own = kF16Sites / kF16Waves;  // sites of a wave
+constexpr int kF16N = kF16Own / 4;              // its column tiles
+
+struct Word3 {
+  uint32_t x, y, z;
+};
+
+// LDS written by some lanes of a wave is read by others after this point.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int MT>
+__global__ void __launch_bounds__(kF16Threads) __attribute__((amdgpu_waves_per_eu(MT == 8 ? 2 : MT == 4 ? 3 : 4)))
+ptc_forward16_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, const uint32_t *__restrict__ links,
+                     const bf16 *__restrict__ in, void *__restrict__ out, int out_f32, int par_arg) {
+  constexpr int NFRAG = MT * 4 * 64, PER = (NFRAG + kF16Threads - 1) / kF16Threads, NT = kF16N;
+  constexpr int kRow = 196;                      // words per site of the output staging (768 bytes and a pad)
+  constexpr int kStage = kF16Sites * (MT == 1 ? 28 : kRow) * 4;  // bytes of it
+  constexpr int kLds = 2 * NFRAG * 16 > kStage ? 2 * NFRAG * 16 : kStage;
+  __shared__ __align__(16) unsigned char smem[kLds];
+  __shared__ int nbL[kF16Waves][8][kF16Own];
+  bf16x8_t *As = reinterpret_cast<bf16x8_t *>(smem);
+  int wl = xcd_remap(blockIdx.x, gridDim.x);
+  const int par = par_arg < 0 ? (wl & 1) : par_arg;
+  if (par_arg < 0) wl >>= 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 3, sl = (lane >> 2) & 3, kg = lane >> 4;
+  const int64_t vh = q.g.Vh, vs = vh * 16;
+  const int s0 = wl * kF16Sites + kF16Own * wave;  // sites beyond the last repeat it; they are not stored
+  const bf16x8_t *A = (const bf16x8_t *)L.A;
+  static_assert(kF16Own * 8 == 64, "one neighbour entry per lane");
+  nbL[wave][lane >> 3][lane & 7] =
+      nbr[((int64_t)par * 8 + (lane >> 3)) * vh + min(s0 + (lane & 7), (int)vh - 1)] & 0x7fffffff;
+  f32x4_t acc[MT][NT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[t][n] = f32x4_t{0, 0, 0, 0};
+
+  bf16x8_t ap[PER];
+  auto load_a1 = [&](int p, int k) __attribute__((always_inline)) {
+    const int e = (threadIdx.x + k * kF16Threads) % NFRAG, t = min(e >> 8, L.mtiles - 1);
+    ap[k] = A[((size_t)t * L.fw_ks + 4 * p + ((e >> 6) & 3)) * 64 + (e & 63)];
+  };
+  auto store_a = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) As[buf * NFRAG + (threadIdx.x + k * kF16Threads) % NFRAG] = ap[k];
+  };
+  const uint32_t *same = reinterpret_cast<const uint32_t *>(in) + (int64_t)par * vs * 12;
+  const uint32_t *other = reinterpret_cast<const uint32_t *>(in) + (int64_t)(1 - par) * vs * 12;
+  Word3 raw[NT][4], lw[NT];
+  // The loads of path p in 8 parts, issued between the products of path p - 1:
+  // all at once they hold up every wave's products until the last is accepted.
+  auto issue = [&](int p, int part) __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      if (part / 2 != n) continue;  // parts 0 .. 2 NT - 1: half of tile n's channels
+      const int64_t nb = nbL[wave][p - 1][4 * n + sl], s = min(s0 + 4 * n + sl, (int)vh - 1);
+      if (part % 2 == 0)
+        lw[n] = *reinterpret_cast<const Word3 *>(links + (((int64_t)par * 8 + p - 1) * vh + s) * 9 + 3 * min(j, 2));
+      const uint32_t *r = other + nb * 192 + kg * 12 + 3 * j;
+#pragma unroll
+      for (int ks = 2 * (part % 2); ks < 2 * (part % 2) + 2; ++ks) raw[n][ks] = *reinterpret_cast<const Word3 *>(r + 48 * ks);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (part == 2 * NT + k * 3 / PER) load_a1(p, k);  // parts 2 NT ..: the weights
+  };
+  uint4 b[NT][4];
+  // Products of the path in buffer buf, 8 parts of 4 MT / 8 (K step, m-tile) steps
+  // (one part for few m-tiles); a part's weights are read from LDS one part ahead.
+  constexpr int STEPS = 4 * MT, PARTS = STEPS >= 8 ? 8 : 1, SP = STEPS / PARTS;
+  auto products = [&](int buf, int next) __attribute__((always_inline)) {
+    const bf16x8_t *a0 = As + buf * NFRAG + lane;
+    auto frag = [&](int i) { return a0[((i % MT) * 4 + i / MT) * 64]; };  // step i: m-tile i % MT, K step i / MT
+    bf16x8_t a[2][SP];
+#pragma unroll
+    for (int m = 0; m < SP; ++m) a[0][m] = frag(m);
+#pragma unroll
+    for (int c = 0; c < PARTS; ++c) {
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PARTS == 8)
+        issue(next, c);
+      else
+#pragma unroll
+        for (int k = 0; k < 8; ++k) issue(next, k);
+      if (c + 1 < PARTS)
+#pragma unroll
+        for (int m = 0; m < SP; ++m) a[(c + 1) & 1][m] = frag((c + 1) * SP + m);
+#pragma unroll
+      for (int m = 0; m < SP; ++m) {
+        const int i = c * SP + m;
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+          acc[i % MT][n] = mfma_bf16(a[c & 1][m], __builtin_bit_cast(bf16x8_t, b[n][i / MT]), acc[i % MT][n]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // identity path: the words of colour j
+#pragma unroll
+  for (int k = 0; k < PER; ++k) load_a1(0, k);
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const uint32_t *r = same + (int64_t)min(s0 + 4 * n + sl, (int)vh - 1) * 192 + kg * 12 + min(j, 2);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) b[n][ks] = make_uint4(r[48 * ks], r[48 * ks + 3], r[48 * ks + 6], r[48 * ks + 9]);
+  }
+  store_a(0);
+  __syncthreads();
+  products(0, 1);
+  store_a(1);
+#pragma unroll 1
+  for (int p = 1; p < 9; ++p) {
+    // transport of path p
+    const mf_f4 zero4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      // real parts: (Re, -Im); imaginary parts: (Im, Re)
+      const uint32_t x[3] = {lw[n].x, lw[n].y, lw[n].z};
+      uint32_t y[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) y[c] = ((x[c] >> 16) | (x[c] << 16)) ^ 0x00008000u;
+      const mf_s4 x0 = __builtin_bit_cast(mf_s4, u32x2_t{x[0], x[1]}), x1 = __builtin_bit_cast(mf_s4, u32x2_t{x[2], 0u});
+      const mf_s4 y0 = __builtin_bit_cast(mf_s4, u32x2_t{y[0], y[1]}), y1 = __builtin_bit_cast(mf_s4, u32x2_t{y[2], 0u});
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const mf_s4 v0 = __builtin_bit_cast(mf_s4, u32x2_t{raw[n][ks].x, raw[n][ks].y});
+        const mf_s4 v1 = __builtin_bit_cast(mf_s4, u32x2_t{raw[n][ks].z, 0u});
+        mf_f4 re = Mf4<bf16>::mma(v0, x0, zero4), im = Mf4<bf16>::mma(v0, y0, zero4);
+        re = Mf4<bf16>::mma(v1, x1, re);
+        im = Mf4<bf16>::mma(v1, y1, im);
+        b[n][ks] = make_uint4(__builtin_bit_cast(uint32_t, pack_bf16x2(re[0], im[0])),
+                              __builtin_bit_cast(uint32_t, pack_bf16x2(re[1], im[1])),
+                              __builtin_bit_cast(uint32_t, pack_bf16x2(re[2], im[2])),
+                              __builtin_bit_cast(uint32_t, pack_bf16x2(re[3], im[3])));
+      }
+    }
+    __syncthreads();  // the weights of path p are in LDS, those of p - 1 have been used
+    products(p & 1, min(p + 1, 8));
+    store_a((p + 1) & 1);
+  }
+  __syncthreads();
+  // Row 16 t + 4 kg + jj is channel 2 t + kg / 2, spin 2 (kg % 2) + jj / 2, part
+  // jj % 2; column 16 n + 4 sl + j is site 4 n + sl, colour j. Staged per wave in
+  // the order of the output, then stored in 16-byte pieces.
+  uint32_t *st = reinterpret_cast<uint32_t *>(smem) + wave * kF16Own * (MT == 1 ? 28 : kRow);
+  if (out_f32) {  // one channel, FP32 packed spinor: [site][24 reals]
+    if (j < 3 && kg < 2)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          *reinterpret_cast<float2 *>(st + (4 * n + sl) * 28 + (2 * kg + h) * 6 + 2 * j) =
+              make_float2(acc[0][n][2 * h], acc[0][n][2 * h + 1]);
+    wave_lds_fence();
+    float *blk = (float *)out + (int64_t)par * vh * 24;
+    if (const int k = lane >> 3, site = lane & 7; k < 6) {
+      if (s0 + site < vh)
+        *reinterpret_cast<float4 *>(blk + ((int64_t)k * vh + s0 + site) * 4) =
+            *reinterpret_cast<const float4 *>(st + site * 28 + 4 * k);
+    }
+    return;
+  }
+  if (j < 3)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int o = 2 * t + (kg >> 1);
+      if (o >= L.cout) continue;
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          st[(4 * n + sl) * (MT == 1 ? 28 : kRow) + o * 12 + (2 * (kg & 1) + h) * 3 + j] =
+              __builtin_bit_cast(uint32_t, pack_bf16x2(acc[t][n][2 * h], acc[t][n][2 * h + 1]));
+    }
+  wave_lds_fence();
+  const int per = L.cout * 3;  // pieces per site
+  uint4 *blk = reinterpret_cast<uint4 *>((bf16 *)out) + ((int64_t)par * vh + s0) * per;
+  for (int e = lane; e < kF16Own * per; e += 64) {
+    const int site = e / per;
+    if (s0 + site < vh) blk[e] = *reinterpret_cast<const uint4 *>(st + site * (MT == 1 ? 28 : kRow) + 4 * (e - site * per));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -730,7 +767,7 @@ ptc_bwd_data_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, const 
       fetch(next, pn, e);
       e1 = entry(min(p + 2, 8));
       __builtin_amdgcn_sched_barrier(0);
-      const Link<float> U = unpack_link<RC, float>(f.lv);
+      const Link<float> U = ptc_link<RC>(f.lv);
       // the matrix products of tile t + 1 run beside the transport of tile t;
       // the barriers keep the compiler from opening more tiles (it spills)
       f32x4_t C[2][3];
@@ -858,10 +895,9 @@ ptc_bwd_weight_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, cons
         load_site<float, RC, float>(q.gauge + (int64_t)(2 * mu + (fwd ? par : 1 - par)) * vh * RC, vh, fwd ? s : n,
                                     lv);
       }
-      const bf16 *blk = in + (int64_t)(p == 0 ? par : 1 - par) * vs * 24;
+      const uint4 *y = reinterpret_cast<const uint4 *>(in) + ((p == 0 ? par : 1 - par) * vs + (int64_t)n * L.cin + i) * 3;
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        yr[c] = *reinterpret_cast<const uint4 *>(blk + ((int64_t)c * vs + (int64_t)n * L.cin + i) * 8);
+      for (int c = 0; c < 3; ++c) yr[c] = y[c];
     };
     if (last < first) return;
     int buf = 0, e1 = entry(first);
@@ -889,7 +925,7 @@ ptc_bwd_weight_kernel(PtcGeo q, PtcLayerDev L, const int *__restrict__ nbr, cons
 #pragma unroll
           for (int c = 0; c < 3; ++c) *reinterpret_cast<uint32_t *>(Bb + sp * kWgRow + 2 * c * kTile) = yw[3 * sp + c];
       } else {
-        const Link<float> U0 = unpack_link<RC, float>(lv);
+        const Link<float> U0 = ptc_link<RC>(lv);
         // U, or U^+ for a backward hop, times the boundary sign, on one spin at a time
         auto apply = [&](auto adj) __attribute__((always_inline)) {
 #pragma unroll
@@ -1055,47 +1091,44 @@ hipError_t launch_ptc_nbr(const Geom &g, int *tab, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_ptc_forward(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *in, void *out,
-                              int out_f32, int par, int variant, int zero_par, hipStream_t st) {
+hipError_t launch_ptc_links(const PtcGeo &q, const int *nbr, void *tab, hipStream_t st) {
+  hipLaunchKernelGGL(ptc_link_kernel, dim3((q.g.Vh + 255) / 256, 16), dim3(256), 0, st, q, nbr, (uint32_t *)tab);
+  return hipGetLastError();
+}
+
+hipError_t launch_ptc_forward(const PtcGeo &q, const PtcLayerDev &L, const int *nbr, const void *links, const void *in,
+                              void *out, int out_f32, int par, int variant, int zero_par, hipStream_t st) {
   // LDS staging of the output tile: BF16 up to 16 channels; FP32 one channel
   if (out_f32 && L.cout != 1) return hipErrorInvalidValue;
   if (par < -1 || par > 1) return hipErrorInvalidValue;
   const int npar = par < 0 ? 2 : 1;  // par -1: both parities in one launch
   switch (variant) {
-#define PTC_FWD_RC(NS, WPE, PIPE, NTH, RC)                                                                   \
-  hipLaunchKernelGGL((ptc_forward_kernel<NS, WPE, PIPE, NTH, RC>), dim3(npar * ((q.g.Vh + NS - 1) / NS)),         \
-                     dim3(NTH), 0, st, q, L, nbr, (const bf16 *)in, out, out_f32, par, zero_par)
-#define PTC_FWD(NS, WPE, PIPE, NTH)              \
-  if constexpr (PIPE == 0) {                     \
-    PTC_FWD_RC(NS, WPE, PIPE, NTH, 18);          \
-  } else if (q.recon == 18) {                    \
-    PTC_FWD_RC(NS, WPE, PIPE, NTH, 18);          \
-  } else {                                       \
-    PTC_FWD_RC(NS, WPE, PIPE, NTH, 12);          \
-  }                                              \
+#define PTC_FWD(NS)                                                                                        \
+  hipLaunchKernelGGL((ptc_forward_kernel<NS>), dim3(npar * ((q.g.Vh + NS - 1) / NS)), dim3(kPtcThreads), 0, \
+                     st, q, L, nbr, (const bf16 *)in, out, out_f32, par, zero_par);                         \
   break;
-    case 642: PTC_FWD(64, 2, 0, 256)
-    case 322: PTC_FWD(32, 2, 0, 256)
-    // the pipelined 16-channel path: 256 threads (8 per site) at 2 or 3 waves
-    // per SIMD, or 512 threads (16 per site) at 3 or 4; colour products on
-    // dot2 (..1) or on the matrix cores (..2). It reads every path, so no
-    // input parity may be known zero.
-    case 3221: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 2, 1, 256)
-    case 3231: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 1, 256)
-    case 3222: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 2, 2, 256)
-    case 3232: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 2, 256)
-    case 5031: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 1, 512)
-    case 5041: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 4, 1, 512)
-    case 5032: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 2, 512)
-    case 5042: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 4, 2, 512)
-    // split forms (512 threads: 4 waves transport, 4 multiply), at 3 or 4 waves per SIMD
-    case 5033: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 3, 512)
-    case 5043: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 4, 3, 512)
-    case 5034: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 3, 4, 512)
-    case 5044: if (L.cin != 16 || zero_par >= 0) return hipErrorInvalidValue; PTC_FWD(32, 4, 4, 512)
-    default: return hipErrorInvalidValue;
+    case 642: PTC_FWD(64)
+    case 322: PTC_FWD(32)
 #undef PTC_FWD
-#undef PTC_FWD_RC
+    case kPtcForward16: {
+      // it reads every path, so no input parity may be known zero
+      if (L.cin != 16 || zero_par >= 0 || !links) return hipErrorInvalidValue;
+      const dim3 grid(npar * ((q.g.Vh + kF16Sites - 1) / kF16Sites)), block(kF16Threads);
+#define PTC_F16(MT)                                                                                        \
+  hipLaunchKernelGGL((ptc_forward16_kernel<MT>), grid, block, 0, st, q, L, nbr, (const uint32_t *)links,    \
+                     (const bf16 *)in, out, out_f32, par)
+      if (L.mtiles == 1)
+        PTC_F16(1);
+      else if (L.mtiles == 2)
+        PTC_F16(2);
+      else if (L.mtiles <= 4)
+        PTC_F16(4);
+      else
+        PTC_F16(8);
+#undef PTC_F16
+      break;
+    }
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -1107,9 +1140,9 @@ __global__ void ptc_input_kernel(int64_t vh, const float *in_even, bf16 *act) {
   if (s >= vh) return;
   float r[24];
   load_spinor_reals<float, 24, float>(in_even, vh, s, r);
-  store_chunks<bf16, 24, 8, float>(act, vh, s, r);
+  store_chunks<bf16, 24, 8, float>(act + s * 24, 1, 0, r);
   float z[24] = {};
-  store_chunks<bf16, 24, 8, float>(act + vh * 24, vh, s, z);
+  store_chunks<bf16, 24, 8, float>(act + (vh + s) * 24, 1, 0, z);
 }
 
 hipError_t launch_ptc_input(int64_t vh, const void *in_even, void *act, hipStream_t st) {

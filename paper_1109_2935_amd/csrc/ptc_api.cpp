@@ -76,6 +76,18 @@ static lqcd_status ptc_geo(lqcd_context *ctx, const lqcd_operator *op, OpInfo *i
   return LQCD_OK;
 }
 
+// The form of the 16-input-channel layers. LQCD_PTC_VARIANT=642 or 322 takes the
+// general form (so that tests can check it); the numbers of the other forms
+// there have been name the one for 16 channels.
+static int forward16_variant() {
+  const char *forced = std::getenv("LQCD_PTC_VARIANT");
+  if (!forced) return kPtcForward16;
+  const int v = std::atoi(forced);
+  for (int f : {3221, 3231, 3222, 3232, 5031, 5041, 5032, 5042, 5033, 5043, 5034, 5044})
+    if (v == f) return kPtcForward16;
+  return v;
+}
+
 // Forward pass; activation k (input of layer k) is kept in acts[k] (full
 // lattice, channel-interleaved BF16), the output y (even sites, FP32 packed
 // spinor) goes to y_even.
@@ -85,40 +97,42 @@ static lqcd_status ptc_forward_all(lqcd_context *ctx, const PtcPlan &plan, const
   void *nbr;
   TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 5, 2 * 8 * vh * sizeof(int), &nbr));
   TRY(hip_check(ctx, launch_ptc_nbr(q.g, (int *)nbr, st), "ptc neighbour table"));
+  void *links = nullptr;
+  for (int l = 1; l < plan.nl && !links; ++l)
+    if (plan.layers[l].cin == 16) {
+      TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 7, ptc_link_bytes(vh), &links));
+      TRY(hip_check(ctx, launch_ptc_links(q, (const int *)nbr, links, st), "ptc link table"));
+    }
   // layer-0 input: r on even sites, zero on odd sites
   TRY(hip_check(ctx, launch_ptc_input((int64_t)vh, in_even, acts[0], st), "ptc input"));
   for (int l = 0; l < plan.nl; ++l) {
     const bool last = l == plan.nl - 1;
     const PtcLayerDev &L = plan.layers[l];
     void *out = last ? y_even : acts[l + 1];
-    // sites per workgroup (and, for 16 input channels, the pipelined form and
-    // its waves per SIMD): timed once per layer shape and geometry
-    std::ostringstream key;
-    key << "ptc_fwd/" << L.cin << "-" << L.cout << "/" << geom_key(q.g);
     // the layer-0 input (r on even sites) vanishes on odd sites
     const int zero_par = l == 0 ? 1 : -1;
-    const std::vector<int> cands =
-        L.cin == 16 && zero_par < 0 ? std::vector<int>{642,  3221, 3231, 3222, 3232, 5031, 5041,
-                                                      5032, 5042, 5033, 5043, 5034, 5044}
-                                    : std::vector<int>{642, 322};
-    // LQCD_PTC_VARIANT=<form> forces the form of the 16-input-channel layers
-    // (so that tests can check every form against the oracle)
-    const char *forced = std::getenv("LQCD_PTC_VARIANT");
-    const int variant =
-        (forced && L.cin == 16 && zero_par < 0)
-            ? std::atoi(forced)
-            : tune_pick(ctx, key.str(), cands, 642, true, st, [&](int v) {
-                return launch_ptc_forward(q, L, (const int *)nbr, acts[l], out, last, 0, v, zero_par, st);
-              });
+    int variant;
+    if (L.cin == 16) {
+      variant = forward16_variant();
+    } else {
+      // sites per workgroup: timed once per layer shape and geometry
+      std::ostringstream key;
+      key << "ptc_fwd/" << L.cin << "-" << L.cout << "/" << geom_key(q.g);
+      variant = tune_pick(ctx, key.str(), {642, 322}, 642, true, st, [&](int v) {
+        return launch_ptc_forward(q, L, (const int *)nbr, links, acts[l], out, last, 0, v, zero_par, st);
+      });
+    }
     // the last layer's output lives on even sites; 16-channel layers compute
     // both parities in one launch (a third less memory traffic, same time),
     // the first layer (only one path per parity carries data) one per launch
     if (last || zero_par >= 0) {
       for (int par = 0; par < (last ? 1 : 2); ++par)
-        TRY(hip_check(ctx, launch_ptc_forward(q, L, (const int *)nbr, acts[l], out, last, par, variant, zero_par, st),
+        TRY(hip_check(ctx, launch_ptc_forward(q, L, (const int *)nbr, links, acts[l], out, last, par, variant, zero_par,
+                                              st),
                       "ptc forward"));
     } else {
-      TRY(hip_check(ctx, launch_ptc_forward(q, L, (const int *)nbr, acts[l], out, last, -1, variant, zero_par, st),
+      TRY(hip_check(ctx, launch_ptc_forward(q, L, (const int *)nbr, links, acts[l], out, last, -1, variant, zero_par,
+                                            st),
                     "ptc forward"));
     }
   }

@@ -7,11 +7,8 @@
 // is kept in the context. With LQCD_TUNE_CACHE=<file> results are also read
 // from and appended to a text file ("key<TAB>value" lines) tagged with the
 // device architecture; LQCD_TUNE=0 disables timing (fallback values).
-// The candidates of the stencil and batch kernels compute the same result
-// (each output element is written by one thread with a fixed summation
-// order). The network's forward forms differ in the order of their FP32 sums
-// (dot2 or matrix-core colour products), so there the choice can change an
-// output by BF16 roundings; LQCD_PTC_VARIANT or a cache file fixes it.
+// The candidates of a kernel compute the same result (each output element is
+// written by one thread with a fixed summation order).
 #include <hip/hip_runtime.h>
 
 #include <cstdio>

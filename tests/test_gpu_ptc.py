@@ -86,6 +86,30 @@ def test_ptc_forward_every_form(ctx, form, dims, recon, monkeypatch):
     check(got, ref, 2e-2)
 
 
+# the form for 16 input channels at every count of output tiles, on lattices of
+# fewer sites than a wave or a workgroup owns and with a remainder of both (8,
+# 96 and 72 sites per parity); the three-layer bound of the note above, and the
+# same bits from a second call
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 2, 4), (2, 2, 6, 6)])
+@pytest.mark.parametrize("cout", [1, 2, 3, 4, 8, 12, 16])
+def test_ptc_forward_from_sixteen_channels(ctx, cout, dims, recon):
+    channels = (1, 16, 1) if cout == 1 else (1, 16, cout, 1)
+    U = synth.gauge_field(dims, 0.25, 141)
+    op32 = ops.wilson_clover(ctx, U, dims, 0.124, 1.0, 1, recon)
+    net = ptc.Network(ctx, channels)
+    Ws = weights_c64(optc.init_weights(142, channels=channels))
+    net.set_weights(Ws)
+    mask = oracle.parity_mask(dims, 0)
+    r = on_parity(synth.gaussian_spinor(dims, 143), mask)
+    out, again = op32.spinor(), op32.spinor()
+    net.apply(op32, out, op32.import_spinor(r, 0))
+    ref, _ = optc.forward(dims, U, r, Ws, mask)
+    check(np_of(op32.export_spinor(out, 0)), ref, 1.5e-2)
+    net.apply(op32, again, op32.import_spinor(r, 0))
+    assert torch.equal(out, again)
+
+
 def test_ptc_gauge_equivariance_on_gpu(ctx):
     channels = (1, 4, 4, 1)
     U = synth.gauge_field(DIMS, 0.25, 71)
