@@ -264,7 +264,8 @@ lqcd_status schur_apply(lqcd_context *ctx, const OpInfo &info, const Geom &g, vo
 // workgroup with the block in LDS (blocks equal to the tiles, 16-bit
 // storage), x in memory (1) or in registers (2); forms 3 and 4 are 1 and 2
 // with twice the threads and half the sites per thread (blocks with at least
-// two sites per thread of 512; elsewhere they run as 1 and 2).
+// two sites per thread of 512; elsewhere, and with FP16 storage, whose kernel has
+// one launch shape, they run as 1 and 2).
 static lqcd_status schwarz_form(lqcd_context *ctx, const OpInfo &info, const Geom &g, const lqcd_schwarz_params *prm,
                                 void *out, const void *in, int slot0, hipStream_t st, int form) {
   const lqcd_operator *op = info.op;
@@ -380,7 +381,7 @@ lqcd_status schwarz_apply(lqcd_context *ctx, const OpInfo &info, const lqcd_schw
       const std::string key = "schwarz p" + std::to_string(info.prec) + " r" + std::to_string(info.recon) + " " +
                               geom_key(g) + " m" + std::to_string(prm->mr_steps) + " c" + std::to_string(prm->cycles);
       std::vector<int> cands = {2, 1, 0};
-      if (sap_block_wide_fits(info.g.Vt2)) cands = {4, 3, 2, 1, 0};
+      if (info.prec != LQCD_F16 && sap_block_wide_fits(info.g.Vt2)) cands = {4, 3, 2, 1, 0};
       form = tune_pick(ctx, key, cands, 2, out != in, st, [&](int c) {
         return schwarz_form(ctx, info, g, prm, out, in, slot0, st, c) == LQCD_OK ? hipSuccess : hipErrorUnknown;
       });

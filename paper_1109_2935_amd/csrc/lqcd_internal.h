@@ -164,7 +164,7 @@ struct SapLaunch {
   int steps;
   int first;
   int xreg;  // x kept in registers (else read and written in memory each step)
-  int wide;  // twice the threads, half the sites per thread (sap_block_wide_fits)
+  int wide;  // twice the threads, half the sites per thread (sap_block_wide_fits; FP16 always takes up to 1024)
 };
 hipError_t launch_sap_block(const SapLaunch &l, hipStream_t st);
 int sap_block_spt(int vt2);  // sites per thread of that launch; 0: blocks of vt2 sites do not fit

@@ -98,6 +98,31 @@ def test_block_form_matches_launches(ctx, monkeypatch, case, cycles, prec, recon
     check(np_of(o.export_spinor(outs[2], 0)), ref, SCHWARZ_TOL[prec] if cycles == 0 else 1.4 * SCHWARZ_TOL[prec])
 
 
+# The FP16 kernel where its layout changes: one wave per block (64 sites), one
+# slab of 1024 threads, two slabs of 768 and of 1024 (their t in the spare and in
+# the wrapped region), and blocks spanning the lattice along one direction each
+# (the antiperiodic sign along t), against the oracle within the bound above and
+# against the launches within a tenth of it.
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims,block", [((4, 4, 4, 8), (2, 4, 4, 4)), ((8, 4, 8, 8), (4, 4, 4, 2)),
+                                        ((16, 8, 8, 8), (8, 8, 8, 4)), ((24, 8, 8, 8), (12, 8, 8, 4)),
+                                        ((8, 16, 8, 16), (8, 8, 8, 8)), ((8, 16, 16, 8), (8, 8, 8, 8)),
+                                        ((16, 8, 16, 8), (8, 8, 8, 4)), ((8, 8, 8, 4), (4, 4, 4, 4))])
+def test_fp16_block_kernel_layouts(ctx, monkeypatch, dims, block, recon):
+    U, psi, Ud = Fields.get(dims)
+    o = ops.wilson_clover(ctx, U, dims, 0.124, 1.0, 2, recon, tile=block, bc_t=-1, U_device=Ud)
+    ref_op = oracle.WilsonClover(dims, U, 0.124, 1.0, bc_t=-1)
+    src = on_parity(psi, ref_op.even)
+    prm = ops.schwarz_params(block, 3, 0)
+    inp = o.import_spinor(src, 0)
+    outs = [np_of(o.export_spinor(run_form(ctx, monkeypatch, o, prm, inp, f), 0)) for f in (0, 1, 2)]
+    from oracle import solvers
+    ref = solvers.schwarz(ref_op, src, block, 3)
+    for f in (1, 2):
+        check(outs[f], ref, SCHWARZ_TOL[2], "form %d" % f)
+        check(outs[f], outs[0], 0.1 * SCHWARZ_TOL[2], "form %d against the launches" % f)
+
+
 def test_block_form_omega_and_repeat(ctx, monkeypatch):
     """Over-relaxed MR in the block form agrees with the launches, also for two
     calls in a row (the second on a new input)."""
