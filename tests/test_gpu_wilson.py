@@ -66,6 +66,20 @@ def test_dslash_parity(ctx, layout, prec, recon, dagger):
         check(got, ref, TOL[prec], "parity %d" % p)
 
 
+# grids of every remainder over the 8 XCDs (544 .. 1056 sites of a parity in workgroups
+# of 64 to 256): every site is computed once, by whichever XCD owns it
+@pytest.mark.parametrize("lt", [34, 38, 42, 46, 50, 54, 58, 62, 66])
+def test_dslash_any_number_of_workgroups(ctx, lt):
+    dims = (4, 4, 2, lt)
+    U, psi, _ = Fields.get(dims)
+    o = make_op(ctx, dims, 2, 12)
+    src = on_parity(psi, oracle.parity_mask(dims, 1))
+    out = o.spinor()
+    L.lqcd_dslash(ctx, o.op, out, o.import_spinor(src, 1), 0, 0)
+    ref = oracle.wilson_dslash(dims, U, src, bc_t=-1, out_parity=0)
+    check(np_of(o.export_spinor(out, 0)), ref, TOL[2], "dslash")
+
+
 @pytest.mark.parametrize("prec,recon", [(0, 18), (1, 12), (2, 12)])
 @pytest.mark.parametrize("block", [(4, 4, 4, 4), (2, 4, 4, 2), (8, 8, 2, 8)])
 def test_dslash_dirichlet_cut(ctx, prec, recon, block):
