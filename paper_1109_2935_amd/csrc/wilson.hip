@@ -246,15 +246,19 @@ __device__ __forceinline__ void wilson_point(const WArgs<S> &a, int s, int rhs, 
     if (!valid) return;
   } else {
     if constexpr (HOPS != kHopsChecked) {
-      // One instantiation for every source count (streamed link loads), so a
-      // site's arithmetic, and its rounding, does not depend on nrhs. The
-      // branch between two calls of it is deliberate: as one basic block with
-      // the epilogue, the clover kernels spill (measured: 700-900 bytes per
-      // lane); split like this they need 137-158 VGPRs and no scratch.
+      // The same arithmetic for every source count, so a site's rounding does not
+      // depend on nrhs. The branch between two calls of it is deliberate: as one
+      // basic block with the epilogue, the clover kernels spill (measured:
+      // 700-900 bytes per lane); split like this they need 137-158 VGPRs and no
+      // scratch. The hopping term of several sources loads links through the
+      // caches, since the workgroups of a site block's other source groups read
+      // them next (24^3 x 48, FP32, 12 sources: 326 us with streamed loads, 310
+      // so); beside clover terms, which are cached then, streamed links are the
+      // faster (12 FP16 sources, Schur matvec: 499 against 551 us).
       if (a.nrhs == 1)
         wilson_hops_pipelined<true, S, R, RECON>(a, x, s, rhs, sgn, acc);
       else
-        wilson_hops_pipelined<true, S, R, RECON>(a, x, s, rhs, sgn, acc);
+        wilson_hops_pipelined<MODE != W_HOP, S, R, RECON>(a, x, s, rhs, sgn, acc);
     } else {
       wilson_dir<0, S, R, RECON>(a, x, s, rhs, sgn, acc);
       wilson_dir<1, S, R, RECON>(a, x, s, rhs, sgn, acc);
