@@ -40,16 +40,14 @@ PROFILED_TRAFFIC = {"sources_sha1": "d723e502af221fefc3ae477560ba39812b96399a", 
 def kernel_sources_sha1():
     import hashlib
     h = hashlib.sha1()
-    for f in ("wilson.hip", "lqcd_device.h"):
+    for f in ("wilson.hip", "wilson_device.h", "lqcd_device.h"):
         with open(os.path.join(ROOT, "paper_1109_2935_amd", "csrc", f), "rb") as fh:
             h.update((hashlib.sha1(fh.read()).hexdigest() + "  " + os.path.join("paper_1109_2935_amd", "csrc", f) + "\n").encode())
     return h.hexdigest()
 SCHUR_REALS = {18: 552, 12: 456, 8: 392}   # two fused kernels, per even site
 PREC_BYTES = {0: 8, 1: 4, 2: 2, 3: 2, 4: 2}
-# Link reals of the FP16 Schwarz operator: with the packed-half hops the
-# block-resident K is bound by vector issue, and rebuilding the third link row
-# costs more there than the 50% more link bytes of the full matrix (1.38 ms
-# against 1.58 ms for 8 MR steps at 32^3x64)
+# Link reals of the FP16 Schwarz operator: the full matrices (8 MR steps at
+# 32^3x64 take 1.10 ms; 0.91 ms with 12 reals and the third row rebuilt)
 K_RECON = 18
 PREC_NAME = {0: "f64", 1: "f32", 2: "f16", 3: "bf16", 4: "half"}
 # 16-bit fixed point adds an FP32 norm per site to every spinor and clover

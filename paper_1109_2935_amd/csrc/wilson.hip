@@ -250,15 +250,19 @@ __device__ __forceinline__ void wilson_point(const WArgs<S> &a, int s, int rhs, 
       // depend on nrhs. The branch between two calls of it is deliberate: as one
       // basic block with the epilogue, the clover kernels spill (measured:
       // 700-900 bytes per lane); split like this they need 137-158 VGPRs and no
-      // scratch. The hopping term of several sources loads links through the
-      // caches, since the workgroups of a site block's other source groups read
-      // them next (24^3 x 48, FP32, 12 sources: 326 us with streamed loads, 310
-      // so); beside clover terms, which are cached then, streamed links are the
-      // faster (12 FP16 sources, Schur matvec: 499 against 551 us).
-      if (a.nrhs == 1)
+      // scratch. Where a site block has several source groups, the hopping term
+      // of FP32 and FP64 fields loads links through the caches, since the next
+      // workgroup reads them again (24^3 x 48, 12 sources: FP32 326 us with
+      // streamed loads, 310 so; FP64 670, 623). One group reads a link once
+      // (4 FP32 sources: 106 streamed, 116 cached); links of 16-bit fields are
+      // half the bytes and take more room than they save (12 FP16 sources: 208,
+      // 230), and beside clover terms, which are cached then, streamed links are
+      // the faster (12 FP16 sources, Schur matvec: 499, 551).
+      constexpr bool kStream = MODE != W_HOP || sizeof(S) == 2;
+      if (a.nrhs == a.rg)
         wilson_hops_pipelined<true, S, R, RECON>(a, x, s, rhs, sgn, acc);
       else
-        wilson_hops_pipelined<MODE != W_HOP, S, R, RECON>(a, x, s, rhs, sgn, acc);
+        wilson_hops_pipelined<kStream, S, R, RECON>(a, x, s, rhs, sgn, acc);
     } else {
       wilson_dir<0, S, R, RECON>(a, x, s, rhs, sgn, acc);
       wilson_dir<1, S, R, RECON>(a, x, s, rhs, sgn, acc);
