@@ -259,10 +259,14 @@ __device__ __forceinline__ void wilson_point(const WArgs<S> &a, int s, int rhs, 
       // 230), and beside clover terms, which are cached then, streamed links are
       // the faster (12 FP16 sources, Schur matvec: 499, 551).
       constexpr bool kStream = MODE != W_HOP || sizeof(S) == 2;
-      if (a.nrhs == a.rg)
+      // (One source has a call of its own, whose addresses the compiler simplifies:
+      // without it launches of 10-30 us took 2% longer.)
+      if (a.nrhs == 1)
+        wilson_hops_pipelined<true, S, R, RECON>(a, x, s, rhs, sgn, acc);
+      else if (kStream || a.nrhs == a.rg)
         wilson_hops_pipelined<true, S, R, RECON>(a, x, s, rhs, sgn, acc);
       else
-        wilson_hops_pipelined<kStream, S, R, RECON>(a, x, s, rhs, sgn, acc);
+        wilson_hops_pipelined<false, S, R, RECON>(a, x, s, rhs, sgn, acc);
     } else {
       wilson_dir<0, S, R, RECON>(a, x, s, rhs, sgn, acc);
       wilson_dir<1, S, R, RECON>(a, x, s, rhs, sgn, acc);
