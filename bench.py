@@ -34,7 +34,7 @@ WILSON_REALS = {18: 192, 12: 144, 8: 112}  # in 24 + out 24 + 8 links per output
 # WRITE_SIZE scaled by the same counters on a 2 GiB device copy (summary under
 # profiles/). Valid only for the kernel sources it was measured on: their hash
 # is checked at run time and the traffic is reported as null when they differ.
-PROFILED_TRAFFIC = {"sources_sha1": "400f9545d0ad8c8a8b4073143eed26ef1baf0260", "bytes_per_launch": 662.7e6}
+PROFILED_TRAFFIC = {"sources_sha1": "9cab9db542a816fcf44ea71f8b8e2f3f8fd42b0c", "bytes_per_launch": 662.8e6}
 
 
 def kernel_sources_sha1():
