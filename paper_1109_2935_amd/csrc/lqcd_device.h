@@ -254,21 +254,34 @@ template <typename R> struct cpx {
 template <typename R> __device__ __forceinline__ cpx<R> mk(R a, R b) { return cpx<R>{a, b}; }
 template <typename R> __device__ __forceinline__ cpx<R> operator+(cpx<R> a, cpx<R> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename R> __device__ __forceinline__ cpx<R> operator-(cpx<R> a, cpx<R> b) { return {a.re - b.re, a.im - b.im}; }
-// Products with the fused operation written out, here and below: which of the
-// two products the compiler would fuse depends on the code around it, and the
-// kernels that share this code give the same result bit for bit.
 template <typename R> __device__ __forceinline__ cpx<R> operator*(cpx<R> a, cpx<R> b) {
-  return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
+  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 template <typename R> __device__ __forceinline__ cpx<R> operator*(R s, cpx<R> a) { return {s * a.re, s * a.im}; }
 template <typename R> __device__ __forceinline__ cpx<R> conj(cpx<R> a) { return {a.re, -a.im}; }
 // conj(a) * b
 template <typename R> __device__ __forceinline__ cpx<R> cmul_conj(cpx<R> a, cpx<R> b) {
-  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
+  return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+}
+// The same products, with FUSED the fused operation written out: which of the two
+// products the compiler fuses depends on the code around it, and the FP32 and FP64
+// Wilson kernels (one thread or eight waves per site) give the same result bit for
+// bit. Kernels without such a twin leave the choice to the compiler: written out
+// there, it costs registers and waves (BF16 Schur matvec, 12 reals, second half:
+// 173 VGPRs and two waves per SIMD instead of 140 and three; both halves at
+// 32^3 x 64 187 instead of 178 us).
+template <bool FUSED, typename R> __device__ __forceinline__ cpx<R> mul(cpx<R> a, cpx<R> b) {
+  if constexpr (FUSED) return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
+  return a * b;
+}
+template <bool FUSED, typename R> __device__ __forceinline__ cpx<R> mul_conj(cpx<R> a, cpx<R> b) {
+  if constexpr (FUSED) return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
+  return cmul_conj(a, b);
 }
 // s * a + b
-template <typename R> __device__ __forceinline__ cpx<R> scale_add(R s, cpx<R> a, cpx<R> b) {
-  return {fma(s, a.re, b.re), fma(s, a.im, b.im)};
+template <bool FUSED, typename R> __device__ __forceinline__ cpx<R> scale_add(R s, cpx<R> a, cpx<R> b) {
+  if constexpr (FUSED) return {fma(s, a.re, b.re), fma(s, a.im, b.im)};
+  return b + s * a;
 }
 // i * a
 template <typename R> __device__ __forceinline__ cpx<R> times_i(cpx<R> a) { return {-a.im, a.re}; }
@@ -296,10 +309,10 @@ template <typename R> struct Link {
   cpx<R> m[3][3];
 };
 
-template <typename R> __device__ __forceinline__ void third_row(Link<R> &u) {
-  u.m[2][0] = conj(u.m[0][1] * u.m[1][2] - u.m[0][2] * u.m[1][1]);
-  u.m[2][1] = conj(u.m[0][2] * u.m[1][0] - u.m[0][0] * u.m[1][2]);
-  u.m[2][2] = conj(u.m[0][0] * u.m[1][1] - u.m[0][1] * u.m[1][0]);
+template <bool FUSED, typename R> __device__ __forceinline__ void third_row(Link<R> &u) {
+  u.m[2][0] = conj(mul<FUSED>(u.m[0][1], u.m[1][2]) - mul<FUSED>(u.m[0][2], u.m[1][1]));
+  u.m[2][1] = conj(mul<FUSED>(u.m[0][2], u.m[1][0]) - mul<FUSED>(u.m[0][0], u.m[1][2]));
+  u.m[2][2] = conj(mul<FUSED>(u.m[0][0], u.m[1][1]) - mul<FUSED>(u.m[0][1], u.m[1][0]));
 }
 
 __device__ __forceinline__ void sincos_r(double a, double *s, double *c) { sincos(a, s, c); }
@@ -312,7 +325,7 @@ __device__ __forceinline__ void sincos_r(float a, float *s, float *c) {
   *c = __builtin_amdgcn_cosf(t);
 }
 
-template <int RECON, typename R> __device__ __forceinline__ Link<R> unpack_link(const R *v) {
+template <int RECON, typename R, bool FUSED = false> __device__ __forceinline__ Link<R> unpack_link(const R *v) {
   Link<R> u;
   if constexpr (RECON == 18) {
 #pragma unroll
@@ -324,7 +337,7 @@ template <int RECON, typename R> __device__ __forceinline__ Link<R> unpack_link(
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) u.m[i][j] = mk<R>(v[6 * i + 2 * j], v[6 * i + 2 * j + 1]);
-    third_row(u);
+    third_row<FUSED>(u);
   } else {
     const cpx<R> a2 = mk<R>(v[0], v[1]), a3 = mk<R>(v[2], v[3]), b1 = mk<R>(v[4], v[5]);
     const R N = a2.re * a2.re + a2.im * a2.im + a3.re * a3.re + a3.im * a3.im;
@@ -340,28 +353,28 @@ template <int RECON, typename R> __device__ __forceinline__ Link<R> unpack_link(
     u.m[0][0] = a1; u.m[0][1] = a2; u.m[0][2] = a3;
     u.m[1][0] = b1;
     u.m[2][0] = c1;
-    u.m[1][1] = (-inv) * (ca3 * cc1 + ca1 * a2 * b1);
-    u.m[1][2] = inv * (ca2 * cc1 - ca1 * a3 * b1);
-    u.m[2][1] = inv * (cb1 * ca3 - ca1 * a2 * c1);
-    u.m[2][2] = (-inv) * (ca2 * cb1 + ca1 * a3 * c1);
+    u.m[1][1] = (-inv) * (mul<FUSED>(ca3, cc1) + mul<FUSED>(mul<FUSED>(ca1, a2), b1));
+    u.m[1][2] = inv * (mul<FUSED>(ca2, cc1) - mul<FUSED>(mul<FUSED>(ca1, a3), b1));
+    u.m[2][1] = inv * (mul<FUSED>(cb1, ca3) - mul<FUSED>(mul<FUSED>(ca1, a2), c1));
+    u.m[2][2] = (-inv) * (mul<FUSED>(ca2, cb1) + mul<FUSED>(mul<FUSED>(ca1, a3), c1));
   }
   return u;
 }
 
 // out = U v  and  out = U^+ v
-template <typename R> __device__ __forceinline__ void su3_mv(const Link<R> &u, const cpx<R> *v, cpx<R> *out) {
+template <bool FUSED = false, typename R> __device__ __forceinline__ void su3_mv(const Link<R> &u, const cpx<R> *v, cpx<R> *out) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    cpx<R> a = u.m[i][0] * v[0];
+    cpx<R> a = mul<FUSED>(u.m[i][0], v[0]);
     cmac(a, u.m[i][1], v[1]);
     cmac(a, u.m[i][2], v[2]);
     out[i] = a;
   }
 }
-template <typename R> __device__ __forceinline__ void su3_adj_mv(const Link<R> &u, const cpx<R> *v, cpx<R> *out) {
+template <bool FUSED = false, typename R> __device__ __forceinline__ void su3_adj_mv(const Link<R> &u, const cpx<R> *v, cpx<R> *out) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    cpx<R> a = cmul_conj(u.m[0][i], v[0]);
+    cpx<R> a = mul_conj<FUSED>(u.m[0][i], v[0]);
     cmac_conj(a, u.m[1][i], v[1]);
     cmac_conj(a, u.m[2][i], v[2]);
     out[i] = a;

@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(NT) sap_block_kernel(SapArgs<S> a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) res[i][c] = scale_add(a.coef, acc[i][c], res[i][c]);
+        for (int c = 0; c < 3; ++c) res[i][c] = res[i][c] + a.coef * acc[i][c];
       sap_flat(res, qf);
       sap_store<S>(qf, w[p]);
       if constexpr (is_fixed<S>()) {

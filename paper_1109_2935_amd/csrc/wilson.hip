@@ -46,8 +46,8 @@ __device__ __forceinline__ void wilson_dir(const WArgs<S> &a, const Site &x, int
     load_spinor<S, R>(a.in, vs, rhs_index(rhs, n, vh, a.rg), psi);
     project<MU, R>(psi, -sgn, h);
     const Link<R> U = load_link<S, R, RECON>(a.gauge, vh, MU, x.p, s, a.nrhs == 1);
-    su3_mv(U, h[0], u[0]);
-    su3_mv(U, h[1], u[1]);
+    su3_mv<fused_products<S>()>(U, h[0], u[0]);
+    su3_mv<fused_products<S>()>(U, h[1], u[1]);
     if constexpr (MU == 3) {
       const R ph = ((w & 1) && a.g.bc_t < 0) ? R(-1) : R(1);
 #pragma unroll
@@ -65,8 +65,8 @@ __device__ __forceinline__ void wilson_dir(const WArgs<S> &a, const Site &x, int
     load_spinor<S, R>(a.in, vs, rhs_index(rhs, n, vh, a.rg), psi);
     project<MU, R>(psi, sgn, h);
     const Link<R> U = load_link<S, R, RECON>(a.gauge, vh, MU, 1 - x.p, n, a.nrhs == 1);
-    su3_adj_mv(U, h[0], u[0]);
-    su3_adj_mv(U, h[1], u[1]);
+    su3_adj_mv<fused_products<S>()>(U, h[0], u[0]);
+    su3_adj_mv<fused_products<S>()>(U, h[1], u[1]);
     if constexpr (MU == 3) {
       const R ph = ((w & 1) && a.g.bc_t < 0) ? R(-1) : R(1);
 #pragma unroll
@@ -308,12 +308,12 @@ __device__ __forceinline__ void wilson_point(const WArgs<S> &a, int s, int rhs, 
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) res[i][c] = scale_add(coef, acc[i][c], res[i][c]);
+        for (int c = 0; c < 3; ++c) res[i][c] = scale_add<fused_products<S>()>(coef, acc[i][c], res[i][c]);
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) res[i][c] = scale_add(coef, acc[i][c], xv[i][c]);
+        for (int c = 0; c < 3; ++c) res[i][c] = scale_add<fused_products<S>()>(coef, acc[i][c], xv[i][c]);
     }
     if constexpr (REDUCE) {
       // inner products of the values as stored

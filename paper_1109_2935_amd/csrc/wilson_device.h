@@ -199,13 +199,16 @@ __device__ __forceinline__ void store_spinor(S *__restrict__ f, int64_t vh, int 
 // Round to the storage precision and back (what a store followed by a load returns).
 template <typename S, typename R> __device__ __forceinline__ R quantize(R v) { return to_real<R>(Store<S>::from(v)); }
 
+// Storage whose Wilson kernels agree bit for bit with those of wilson_split.hip.
+template <typename S> constexpr bool fused_products() { return sizeof(S) >= 4; }
+
 // stream: the link is read once per launch (one right-hand side)
 template <typename S, typename R, int RECON>
 __device__ __forceinline__ Link<R> load_link(const S *__restrict__ gauge, int64_t vh, int mu, int parity, int s,
                                              bool stream) {
   R v[RECON];
   load_site_once<S, RECON, R>(gauge + (int64_t)(2 * mu + parity) * vh * RECON, vh, s, v, stream);
-  return unpack_link<RECON, R>(v);
+  return unpack_link<RECON, R, fused_products<S>()>(v);
 }
 
 // Clover: per site and chirality block a Hermitian 6x6 (index = spin-in-block*3
@@ -329,13 +332,14 @@ __device__ __forceinline__ void hop_product(const HopIn<S, RECON> &h, R ps, int 
       lv[k] = to_real<R>(h.link[k]);
       if constexpr (is_float16<S>()) __asm__ volatile("" : "+v"(lv[k]));
     }
-    const Link<R> U = unpack_link<RECON, R>(lv);
+    constexpr bool F = fused_products<S>();
+    const Link<R> U = unpack_link<RECON, R, F>(lv);
     if constexpr (DIR > 0) {
-      su3_mv(U, hh[0], u[0]);
-      su3_mv(U, hh[1], u[1]);
+      su3_mv<F>(U, hh[0], u[0]);
+      su3_mv<F>(U, hh[1], u[1]);
     } else {
-      su3_adj_mv(U, hh[0], u[0]);
-      su3_adj_mv(U, hh[1], u[1]);
+      su3_adj_mv<F>(U, hh[0], u[0]);
+      su3_adj_mv<F>(U, hh[1], u[1]);
     }
   }
   if constexpr (MU == 3) {

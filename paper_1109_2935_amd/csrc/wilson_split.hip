@@ -193,9 +193,9 @@ __global__ void __launch_bounds__(kSplitThreads) wilson_split_kernel(WArgs<S> a,
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         if constexpr (CLOV)
-          res[e] = scale_add(coef, acc[e], clover_row_mul(row[e], i0 + e, xv));
+          res[e] = scale_add<true>(coef, acc[e], clover_row_mul(row[e], i0 + e, xv));
         else
-          res[e] = scale_add(coef, acc[e], xv[e]);
+          res[e] = scale_add<true>(coef, acc[e], xv[e]);
       }
   }
   if constexpr (CG != kCgNone) {
