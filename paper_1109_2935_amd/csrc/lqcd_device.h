@@ -580,7 +580,14 @@ __device__ __forceinline__ bool hop_kept(const Geom &g, const Site &x, int step)
 __device__ __forceinline__ int xcd_remap(int wg, int nwg) {
   constexpr int NXCD = 8;
   const int x = wg % NXCD, more = nwg % NXCD;
-  return x * (nwg / NXCD) + (x < more ? x : more) + wg / NXCD;
+  int r = x * (nwg / NXCD) + wg / NXCD;
+  if (more) {
+    // (a branch, kept by the empty asm: the compiler then issues the kernel's argument loads together ahead of
+    // it; as a select it waits for them twice, which costs every launch 0.15 us)
+    __asm__ volatile("");
+    r += x < more ? x : more;
+  }
+  return r;
 }
 
 // Fields of several right-hand sides are stored in blocks of R sources
