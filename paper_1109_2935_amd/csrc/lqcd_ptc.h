@@ -52,9 +52,10 @@ inline size_t ptc_adj_frag_bytes(const PtcLayerDev &L) { return (size_t)L.madj_t
 
 // neighbour table of the 8 hop paths, 2 * 8 * Vh ints (see ptc_nbr_kernel)
 hipError_t launch_ptc_nbr(const Geom &g, int *tab, hipStream_t st);
-// link table of the hop paths for the 16-input-channel form (ptc_link_kernel)
-inline size_t ptc_link_bytes(size_t vh) { return 2 * 8 * vh * 36; }
-hipError_t launch_ptc_links(const PtcGeo &q, const int *nbr, void *tab, hipStream_t st);
+// both tables of the 16-input-channel form: the neighbours, and the links of the
+// hops to sites of the first npar parities (ptc_link_kernel)
+inline size_t ptc_link_bytes(size_t vh, int npar) { return npar * 8 * vh * 36; }
+hipError_t launch_ptc_links(const PtcGeo &q, int npar, int *nbr, void *tab, hipStream_t st);
 // variant: the general form with 64 or 32 sites per workgroup (642, 322), or the
 // form for 16 input channels (which needs `links`)
 constexpr int kPtcForward16 = 16;

@@ -385,16 +385,29 @@ ptc_forward_kernel(PtcGeo q, PtcLayerDev L, const int *nbr, const bf16 *in, void
 // U is rounded to BF16, colour and channel sums are in FP32, and the transported
 // inputs are rounded to BF16, each sum in the order of that form.
 
-// Link table of the hop paths: entry [par][p - 1][s] holds the applied matrix (U,
-// or U^+ for a backward hop, times the boundary sign), 9 words (Re, -Im) in BF16.
-__global__ void __launch_bounds__(256) ptc_link_kernel(PtcGeo q, const int *__restrict__ nbr, uint32_t *__restrict__ tab) {
+// Link table of the hop paths, and the neighbour table (as ptc_nbr_kernel) in the
+// same launch: entry [par][p - 1][s] of the links, for par < npar, holds the applied
+// matrix (U, or U^+ for a backward hop, times the boundary sign), 9 words (Re, -Im)
+// in BF16.
+__global__ void __launch_bounds__(256) ptc_link_kernel(PtcGeo q, int npar, int *__restrict__ nbr,
+                                                       uint32_t *__restrict__ tab) {
   const int64_t vh = q.g.Vh;
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int par = blockIdx.y >> 3, p = blockIdx.y & 7, mu = p >> 1;
   const bool fwd = (p & 1) == 0;
   if (s >= vh) return;
-  const int e = nbr[((int64_t)par * 8 + p) * vh + s];
-  const int64_t ls = fwd ? s : (e & 0x7fffffff);
+  const Site x = decode_site(q.g, (int)s, par);
+  int w, n;
+  switch (mu) {
+    case 0: n = hop<0>(q.g, x, fwd ? 1 : -1, &w); break;
+    case 1: n = hop<1>(q.g, x, fwd ? 1 : -1, &w); break;
+    case 2: n = hop<2>(q.g, x, fwd ? 1 : -1, &w); break;
+    default: n = hop<3>(q.g, x, fwd ? 1 : -1, &w); break;
+  }
+  const int e = n | ((mu == 3 && (w & 1) && q.g.bc_t < 0) << 31);
+  nbr[((int64_t)par * 8 + p) * vh + s] = e;
+  if (par >= npar) return;
+  const int64_t ls = fwd ? s : n;
   const float *base = q.gauge + (int64_t)(2 * mu + (fwd ? par : 1 - par)) * vh * q.recon;
   Link<float> U0;
   if (q.recon == 12) {
@@ -1090,8 +1103,8 @@ hipError_t launch_ptc_nbr(const Geom &g, int *tab, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_ptc_links(const PtcGeo &q, const int *nbr, void *tab, hipStream_t st) {
-  hipLaunchKernelGGL(ptc_link_kernel, dim3((q.g.Vh + 255) / 256, 16), dim3(256), 0, st, q, nbr, (uint32_t *)tab);
+hipError_t launch_ptc_links(const PtcGeo &q, int npar, int *nbr, void *tab, hipStream_t st) {
+  hipLaunchKernelGGL(ptc_link_kernel, dim3((q.g.Vh + 255) / 256, 16), dim3(256), 0, st, q, npar, nbr, (uint32_t *)tab);
   return hipGetLastError();
 }
 

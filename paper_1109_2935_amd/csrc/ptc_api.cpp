@@ -96,13 +96,20 @@ static lqcd_status ptc_forward_all(lqcd_context *ctx, const PtcPlan &plan, const
   const size_t vh = info.vh;
   void *nbr;
   TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 5, 2 * 8 * vh * sizeof(int), &nbr));
-  TRY(hip_check(ctx, launch_ptc_nbr(q.g, (int *)nbr, st), "ptc neighbour table"));
+  // links at the output sites of the layers from 16 channels: the last layer's are
+  // even (of a network whose only such layer is the last, 1-16-1 at 24^3 x 48, both
+  // parities' table would take 80 us to save the layer 62)
+  const int form16 = forward16_variant();
+  int npar = 0;
+  for (int l = 1; l < plan.nl && form16 == kPtcForward16; ++l)
+    if (plan.layers[l].cin == 16) npar = std::max(npar, l == plan.nl - 1 ? 1 : 2);
   void *links = nullptr;
-  for (int l = 1; l < plan.nl && !links; ++l)
-    if (plan.layers[l].cin == 16) {
-      TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 7, ptc_link_bytes(vh), &links));
-      TRY(hip_check(ctx, launch_ptc_links(q, (const int *)nbr, links, st), "ptc link table"));
-    }
+  if (npar) {
+    TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 7, ptc_link_bytes(vh, npar), &links));
+    TRY(hip_check(ctx, launch_ptc_links(q, npar, (int *)nbr, links, st), "ptc neighbour and link tables"));
+  } else {
+    TRY(hip_check(ctx, launch_ptc_nbr(q.g, (int *)nbr, st), "ptc neighbour table"));
+  }
   // layer-0 input: r on even sites, zero on odd sites
   TRY(hip_check(ctx, launch_ptc_input((int64_t)vh, in_even, acts[0], st), "ptc input"));
   for (int l = 0; l < plan.nl; ++l) {
@@ -113,7 +120,7 @@ static lqcd_status ptc_forward_all(lqcd_context *ctx, const PtcPlan &plan, const
     const int zero_par = l == 0 ? 1 : -1;
     int variant;
     if (L.cin == 16) {
-      variant = forward16_variant();
+      variant = form16;
     } else {
       // sites per workgroup: timed once per layer shape and geometry
       std::ostringstream key;
