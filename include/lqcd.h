@@ -44,10 +44,13 @@
  * Environment. LQCD_TUNE=0 disables the autotuner's timing (fixed fallback
  * launch parameters); LQCD_TUNE_CACHE=<file> keeps its choices across
  * processes; LQCD_MRHS_MFMA=1 selects the matrix-core form of the multi-source
- * link products; LQCD_PTC_VARIANT=642 or 322 runs the network's 16-input-channel
- * layers in the general form (for testing; its FP32 sums have another order, so
- * the output changes by BF16 roundings); LQCD_VERBOSE prints the solvers'
- * residual history to stderr. The tuned launch parameters never change a result.
+ * link products; LQCD_VERBOSE prints the solvers' residual history to stderr.
+ * The tuned launch parameters never change a result. The network's layers from 16
+ * channels round the links to BF16 before their colour products; with LQCD_TUNE=0,
+ * and with LQCD_PTC_VARIANT=642 or 322, they run in the general form, which
+ * transports with FP32 links as the other layers do (the output changes by BF16
+ * roundings), takes up to twice the time and spares the 576 bytes of scratch memory
+ * per even site that the BF16 links take (288 if only the last layer has 16).
  */
 #ifndef LQCD_H
 #define LQCD_H

@@ -76,13 +76,21 @@ static lqcd_status ptc_geo(lqcd_context *ctx, const lqcd_operator *op, OpInfo *i
   return LQCD_OK;
 }
 
-// The form of the 16-input-channel layers. LQCD_PTC_VARIANT=642 or 322 takes the
-// general form (so that tests can check it); the numbers of the other forms
-// there have been name the one for 16 channels.
-static int forward16_variant() {
+static std::string forward_key(const PtcLayerDev &L, const Geom &g) {
+  std::ostringstream key;
+  key << "ptc_fwd/" << L.cin << "-" << L.cout << "/" << geom_key(g);
+  return key.str();
+}
+
+// The form of a 16-input-channel layer: the one for 16 channels, which rounds the
+// links to BF16, where the autotuner may choose; the general form, which transports
+// with FP32 links, where it may not (LQCD_TUNE=0, whose fallback it has always been)
+// or where LQCD_PTC_VARIANT or a saved choice names it (642, 322). The numbers of the
+// other forms there have been, all with BF16 links, name the one for 16 channels.
+static int forward16_variant(lqcd_context *ctx, const PtcLayerDev &L, const Geom &g, hipStream_t st) {
   const char *forced = std::getenv("LQCD_PTC_VARIANT");
-  if (!forced) return kPtcForward16;
-  const int v = std::atoi(forced);
+  const int v = forced ? std::atoi(forced) : tune_pick(ctx, forward_key(L, g), {}, 0, false, st, {});
+  if (!forced && v == 0) return ctx->tune_enabled && !ctx->tune_frozen ? kPtcForward16 : 642;
   for (int f : {3221, 3231, 3222, 3232, 5031, 5041, 5032, 5042, 5033, 5043, 5034, 5044})
     if (v == f) return kPtcForward16;
   return v;
@@ -99,10 +107,13 @@ static lqcd_status ptc_forward_all(lqcd_context *ctx, const PtcPlan &plan, const
   // links at the output sites of the layers from 16 channels: the last layer's are
   // even (of a network whose only such layer is the last, 1-16-1 at 24^3 x 48, both
   // parities' table would take 80 us to save the layer 62)
-  const int form16 = forward16_variant();
+  std::vector<int> variants(plan.nl, 0);
   int npar = 0;
-  for (int l = 1; l < plan.nl && form16 == kPtcForward16; ++l)
-    if (plan.layers[l].cin == 16) npar = std::max(npar, l == plan.nl - 1 ? 1 : 2);
+  for (int l = 1; l < plan.nl; ++l) {
+    if (plan.layers[l].cin != 16) continue;
+    variants[l] = forward16_variant(ctx, plan.layers[l], q.g, st);
+    if (variants[l] == kPtcForward16) npar = std::max(npar, l == plan.nl - 1 ? 1 : 2);
+  }
   void *links = nullptr;
   if (npar) {
     TRY(scratch(ctx, kSlotPtc + kPtcMaxLayers + 7, ptc_link_bytes(vh, npar), &links));
@@ -118,14 +129,10 @@ static lqcd_status ptc_forward_all(lqcd_context *ctx, const PtcPlan &plan, const
     void *out = last ? y_even : acts[l + 1];
     // the layer-0 input (r on even sites) vanishes on odd sites
     const int zero_par = l == 0 ? 1 : -1;
-    int variant;
-    if (L.cin == 16) {
-      variant = form16;
-    } else {
+    int variant = variants[l];
+    if (L.cin != 16) {
       // sites per workgroup: timed once per layer shape and geometry
-      std::ostringstream key;
-      key << "ptc_fwd/" << L.cin << "-" << L.cout << "/" << geom_key(q.g);
-      variant = tune_pick(ctx, key.str(), {642, 322}, 642, true, st, [&](int v) {
+      variant = tune_pick(ctx, forward_key(L, q.g), {642, 322}, 642, true, st, [&](int v) {
         return launch_ptc_forward(q, L, (const int *)nbr, links, acts[l], out, last, 0, v, zero_par, st);
       });
     }

@@ -110,6 +110,66 @@ def test_ptc_forward_from_sixteen_channels(ctx, cout, dims, recon):
     assert torch.equal(out, again)
 
 
+# The general form at 16 input channels (64 and 32 sites per workgroup), which no
+# form number above selects, on full workgroups and on one that is partly empty;
+# the four-layer bound of the note above.
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims", [DIMS, (4, 2, 2, 2), (2, 2, 6, 6)])
+@pytest.mark.parametrize("form", [642, 322])
+def test_ptc_forward_general_form_from_sixteen_channels(ctx, form, dims, recon, monkeypatch):
+    channels = (1, 16, 16, 16, 1)
+    U = synth.gauge_field(dims, 0.25, 151)
+    op32 = ops.wilson_clover(ctx, U, dims, 0.124, 1.0, 1, recon)
+    net = ptc.Network(ctx, channels)
+    Ws = weights_c64(optc.init_weights(152, channels=channels))
+    net.set_weights(Ws)
+    r = on_parity(synth.gaussian_spinor(dims, 153), oracle.parity_mask(dims, 0))
+    out = op32.spinor()
+    monkeypatch.setenv("LQCD_PTC_VARIANT", str(form))
+    net.apply(op32, out, op32.import_spinor(r, 0))
+    ref, _ = optc.forward(dims, U, r, Ws, oracle.parity_mask(dims, 0))
+    check(np_of(op32.export_spinor(out, 0)), ref, 2e-2)
+
+
+# Without the autotuner's timing, and where a saved choice names it, layers from 16
+# channels run in the general form, whose links are not rounded to BF16: the bits
+# are those of the forced general form, and not those of the form for 16 channels.
+@pytest.mark.parametrize("how", ["untuned", "saved"])
+def test_ptc_general_form_is_the_untuned_choice(how, monkeypatch, tmp_path):
+    dims, channels = (8, 8, 8, 8), (1, 16, 16, 1)
+    U = synth.gauge_field(dims, 0.25, 161)
+    r = on_parity(synth.gaussian_spinor(dims, 162), oracle.parity_mask(dims, 0))
+    Ws = weights_c64(optc.init_weights(163, channels=channels))
+
+    def run():
+        c = L.lqcd_context_create()
+        op32 = ops.wilson_clover(c, U, dims, 0.124, 1.0, 1, 12)
+        net = ptc.Network(c, channels)
+        net.set_weights(Ws)
+        out = op32.spinor()
+        net.apply(op32, out, op32.import_spinor(r, 0))
+        torch.cuda.synchronize()
+        L.lqcd_context_destroy(c)
+        return out
+
+    for v in ("LQCD_TUNE", "LQCD_TUNE_CACHE", "LQCD_PTC_VARIANT"):
+        monkeypatch.delenv(v, raising=False)
+    tuned = run()
+    monkeypatch.setenv("LQCD_PTC_VARIANT", "642")
+    general = run()
+    monkeypatch.delenv("LQCD_PTC_VARIANT")
+    if how == "untuned":
+        monkeypatch.setenv("LQCD_TUNE", "0")
+    else:
+        arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+        saved = tmp_path / "tune.txt"
+        saved.write_text("".join("%s ptc_fwd/16-%d/8x8x8x8/8x8x8x8\t642\n" % (arch, n) for n in (16, 1)))
+        monkeypatch.setenv("LQCD_TUNE_CACHE", str(saved))
+    got = run()
+    assert torch.equal(got, general)
+    assert not torch.equal(got, tuned)
+
+
 def test_ptc_gauge_equivariance_on_gpu(ctx):
     channels = (1, 4, 4, 1)
     U = synth.gauge_field(DIMS, 0.25, 71)
