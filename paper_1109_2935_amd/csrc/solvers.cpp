@@ -770,13 +770,13 @@ extern "C" lqcd_status lqcd_cg_solve(lqcd_context *ctx, const lqcd_operator *op_
                    }));
       rr_new = rr_new_true = run.rr_new;
       inf.matvecs += 2 * run.done;
-      // a residual that is not a number makes the next |p|^2 one
-      if (run.breakdown || !(rr_new == rr_new)) {
+      // a residual that is not a number makes the next |p|^2 one, if there is a next
+      if (run.breakdown || (!(rr_new == rr_new) && it < prm->max_iter)) {
         inf.matvecs++;
         status = set_error(ctx, LQCD_ERR_BREAKDOWN, "CGNE breakdown: |p| = 0");
         break;
       }
-      if (rr_new > stop) break;  // max_iter
+      if (!(rr_new <= stop)) break;  // max_iter
       inf.matvecs--;  // (the last search direction was not formed)
       rr = run.rr;
     } else {

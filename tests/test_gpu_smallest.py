@@ -101,3 +101,40 @@ def test_cgne_device_iterations_equal_host_loop(ctx, dims, recon, max_iter):
     # FP64 sums in another order: the recurrences amplify 1e-16 by the steps taken
     assert np.allclose(dev[4], host[4], rtol=1e-9)
     assert rel(dev[5], host[5]) < 1e-11
+
+
+def cgne_both_ways(ctx, o, prm_of, x0, b):
+    """The device-driven solve, then the host's loop (which a solve that records its iterates takes)."""
+    import ctypes
+    runs = []
+    for record in (False, True):
+        prm = prm_of()
+        if record:
+            rec, err, zero = o.spinor(nrhs=1), o.spinor(nrhs=1), o.spinor()
+            count = ctypes.c_int32(0)
+            prm.record_r, prm.record_e, prm.record_xstar = rec.data_ptr(), err.data_ptr(), zero.data_ptr()
+            prm.record_every, prm.record_max, prm.record_count = 100000, 1, ctypes.pointer(count)
+        x = x0.clone()
+        try:
+            st, info = L.lqcd_cg_solve(ctx, o.op, None, prm, x, b)
+        except L.LqcdError as e:
+            st, info = e.status, None
+        runs.append((st, info, np_of(o.export_spinor(x, -1))))
+    return runs
+
+
+# A residual that overflows to NaN in an iteration is a breakdown only if another
+# iteration would follow; at max_iter the solve has not converged. Clover entries of
+# 1e198 and a source of 1e-50 keep |p|^2 finite (1e300) and overflow the operator's
+# second application.
+@pytest.mark.parametrize("max_iter", [1, 2])
+def test_cgne_residual_not_a_number(ctx, max_iter):
+    dims = (4, 4, 4, 4)
+    o = ops.wilson_clover(ctx, synth.gauge_field(dims, 0.25, 171), dims, 0.12, 1.0, 0, 18)
+    o._keep["clover"].view(torch.float64).mul_(1e198)
+    b = o.import_spinor(1e-50 * synth.gaussian_spinor(dims, 172), -1)
+    dev, host = cgne_both_ways(ctx, o, lambda: ops.cg_params(1e-10, max_iter), o.spinor(full=True).zero_(), b)
+    assert host[0] == (L.LQCD_ERR_NOT_CONVERGED if max_iter == 1 else L.LQCD_ERR_BREAKDOWN)
+    assert dev[0] == host[0]
+    if max_iter == 1:
+        assert (dev[1].iters, dev[1].matvecs) == (host[1].iters, host[1].matvecs)
