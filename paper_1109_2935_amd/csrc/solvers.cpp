@@ -406,36 +406,40 @@ lqcd_status cg_ahead(Solver &S, const OpInfo &op, CgStep c, void *tmp, int most,
   for (int k = 0; k < kCgRing; ++k) __atomic_store_n(&ctx->cg_ring[k].iter, 0ull, __ATOMIC_RELEASE);
   TRY(S.hip(launch_cg_start(op, c, st->rr, st->pp, S.st), "cg start"));
   st->rr_new = st->rr;
-  int queued = 0;
-  lqcd_status status = LQCD_OK;
-  while (st->done < most) {
-    // two iterations ahead: one runs while the next is enqueued
-    while (queued < most && queued < st->done + 2) {
-      c.iter = ++queued;
-      TRY(S.hip(launch_cg_iteration(op, c, tmp, S.st), "cg iteration"));
+  auto iterate = [&]() -> lqcd_status {
+    int queued = 0;
+    while (st->done < most) {
+      // two iterations ahead: one runs while the next is enqueued
+      while (queued < most && queued < st->done + 2) {
+        c.iter = ++queued;
+        TRY(S.hip(launch_cg_iteration(op, c, tmp, S.st), "cg iteration"));
+      }
+      const unsigned long long want = st->done + 1;
+      CgRing *e = ctx->cg_ring + want % kCgRing;
+      for (int spins = 1; __atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want; ++spins) {
+        if (spins % 1024) continue;
+        const hipError_t q = hipStreamQuery(S.st);
+        if (q == hipErrorNotReady) continue;
+        TRY(S.hip(q, "cg iteration"));  // the stream has drained (or failed)
+        if (__atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want)
+          return set_error(ctx, LQCD_ERR_DEVICE, "cg iteration did not report");
+      }
+      if (!(e->pp > 0)) {
+        st->breakdown = true;
+        break;
+      }
+      st->rr = st->rr_new;
+      st->rr_new = e->rr;
+      ++st->done;
+      seen(st->rr_new, st->rr / e->pp);
+      if (!(st->rr_new > c.stop)) break;
     }
-    const unsigned long long want = st->done + 1;
-    CgRing *e = ctx->cg_ring + want % kCgRing;
-    for (int spins = 1; __atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want; ++spins) {
-      if (spins % 1024) continue;
-      const hipError_t q = hipStreamQuery(S.st);
-      if (q == hipErrorNotReady) continue;
-      status = S.hip(q, "cg iteration");  // the stream has drained (or failed)
-      if (status == LQCD_OK && __atomic_load_n(&e->iter, __ATOMIC_ACQUIRE) != want)
-        status = set_error(ctx, LQCD_ERR_DEVICE, "cg iteration did not report");
-      if (status != LQCD_OK) return status;
-    }
-    if (!(e->pp > 0)) {
-      st->breakdown = true;
-      break;
-    }
-    st->rr = st->rr_new;
-    st->rr_new = e->rr;
-    ++st->done;
-    seen(st->rr_new, st->rr / e->pp);
-    if (!(st->rr_new > c.stop)) break;
-  }
-  return S.hip(hipStreamSynchronize(S.st), "cg iteration");
+    return LQCD_OK;
+  };
+  // iterations may be in flight on every way out, after an error too: they write the context's vectors and ring
+  const lqcd_status status = iterate();
+  const hipError_t drained = hipStreamSynchronize(S.st);
+  return status != LQCD_OK ? status : S.hip(drained, "cg iteration");
 }
 
 // CG or CGNE (the same recurrences as lqcd_cg_solve) on nrhs systems at once:

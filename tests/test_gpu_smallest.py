@@ -138,3 +138,21 @@ def test_cgne_residual_not_a_number(ctx, max_iter):
     assert dev[0] == host[0]
     if max_iter == 1:
         assert (dev[1].iters, dev[1].matvecs) == (host[1].iters, host[1].matvecs)
+
+
+# From a first guess 1e6 times the solution, adding the correction leaves an error of
+# a few 1e-16 * 1e6 in x, so the true residual fails the stop of 1e-10 that the
+# iterated one has passed, and the device's iterations are entered again from it. The
+# solution then meets the stop; two such solutions differ by at most the condition of
+# the operator (below 1e3 here) times twice the stop.
+@pytest.mark.parametrize("dims,recon", [((4, 4, 4, 4), 18), ((8, 4, 6, 8), 12)])
+def test_cgne_device_iterations_after_a_failed_true_residual(ctx, dims, recon):
+    o = ops.wilson_clover(ctx, synth.gauge_field(dims, 0.25, 173), dims, 0.12, 1.0, 0, recon)
+    b = o.import_spinor(synth.gaussian_spinor(dims, 174), -1)
+    x0 = o.import_spinor(1e6 * synth.gaussian_spinor(dims, 175), -1)
+    dev, host = cgne_both_ways(ctx, o, lambda: ops.cg_params(1e-10, 1000), x0, b)
+    for st, info, _ in (dev, host):
+        assert st == L.LQCD_OK, L.lqcd_last_error(ctx)
+        assert info.restarts >= 2
+        assert info.true_residual <= 1e-10 * (1 + 1e-6)
+    assert rel(dev[2], host[2]) < 1e3 * 2e-10
