@@ -45,7 +45,10 @@
  * launch parameters); LQCD_TUNE_CACHE=<file> keeps its choices across
  * processes; LQCD_MRHS_MFMA=1 selects the matrix-core form of the multi-source
  * link products; LQCD_VERBOSE prints the solvers' residual history to stderr.
- * The tuned launch parameters never change a result. The network's layers from 16
+ * The tuned launch parameters never change a result, with one exception: the
+ * Schwarz preconditioner of LQCD_HALF operators times cut launches against the
+ * block-resident forms, which round differently (LQCD_SCHWARZ_FORM=0 .. 4 or a
+ * tuning cache fixes the choice). The network's layers from 16
  * channels round the links to BF16 before their colour products; with LQCD_TUNE=0,
  * and with LQCD_PTC_VARIANT=642 or 322, they run in the general form, which
  * transports with FP32 links as the other layers do (the output changes by BF16

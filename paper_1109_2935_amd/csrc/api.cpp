@@ -356,6 +356,21 @@ static lqcd_status schwarz_form(lqcd_context *ctx, const OpInfo &info, const Geo
   return LQCD_OK;
 }
 
+// FP16 storage: few large blocks are faster as cut launches over the whole lattice
+// (form 0) than one to a workgroup. The block form takes as long for one block as for
+// 256; the launches take longer with the sites. Measured with 8 steps on all blocks
+// (us, launches / block form, 12 link reals | 18):
+//   2048 sites: 48 blocks 326 / 372 | 322 / 343, 81 blocks 433 / 377 | 423 / 342
+//   1536 sites: 32 blocks 183 / 218 | 167 / 205 (6 steps)
+//   1024 sites:  8 blocks 177 / 187 | 175 / 162, 32 blocks 218 / 181 | 191 / 158
+//    512 sites:  4 blocks 175 / 105 | 169 / 96
+// so the line is at a number of sites that grows with the block. The two forms round
+// differently, so the choice is a rule and not a timing: K, and a solve's iterates,
+// are the same in every run. vt2: sites of a block, vh: of the launch (one parity).
+static bool half_takes_launches(int vt2, int recon, int64_t vh) {
+  return vh < (recon == 12 ? 115 * ((int64_t)vt2 - 900) : 100 * ((int64_t)vt2 - 1024));
+}
+
 // Does the block-resident form apply (blocks equal to the tiles, 16-bit
 // storage, 12 or 18 link reals, a block in LDS)?
 static bool schwarz_block_form_fits(const OpInfo &info, const Geom &g) {
@@ -372,19 +387,26 @@ lqcd_status schwarz_apply(lqcd_context *ctx, const OpInfo &info, const lqcd_schw
   if (s) return s;
   int form = 0;
   if (schwarz_block_form_fits(info, g)) {
-    // the forms give the same result; the autotuner keeps the fastest, and
-    // LQCD_SCHWARZ_FORM=0 .. 4 fixes the choice
+    // The block-resident forms give the same result, and with BF16 storage form 0
+    // does too: the autotuner keeps the fastest. With FP16 form 0 is chosen by a
+    // rule; in fixed point it is timed with the others although it rounds
+    // differently. LQCD_SCHWARZ_FORM=0 .. 4 fixes the choice.
     const char *f = std::getenv("LQCD_SCHWARZ_FORM");
+    const bool half = info.prec == LQCD_F16;
     if (f && f[0] >= '0' && f[0] <= '4' && f[1] == 0) {
       form = f[0] - '0';
-    } else {
+    } else if (!half || !half_takes_launches(info.g.Vt2, info.recon, prm->cycles > 0 ? info.vh / 2 : info.vh)) {
       const std::string key = "schwarz p" + std::to_string(info.prec) + " r" + std::to_string(info.recon) + " " +
                               geom_key(g) + " m" + std::to_string(prm->mr_steps) + " c" + std::to_string(prm->cycles);
       std::vector<int> cands = {2, 1, 0};
-      if (info.prec != LQCD_F16 && sap_block_wide_fits(info.g.Vt2)) cands = {4, 3, 2, 1, 0};
+      if (half)
+        cands = {2, 1};
+      else if (sap_block_wide_fits(info.g.Vt2))
+        cands = {4, 3, 2, 1, 0};
       form = tune_pick(ctx, key, cands, 2, out != in, st, [&](int c) {
         return schwarz_form(ctx, info, g, prm, out, in, slot0, st, c) == LQCD_OK ? hipSuccess : hipErrorUnknown;
       });
+      if (half && form == 0) form = 2;  // a choice saved when it was timed
     }
   }
   return schwarz_form(ctx, info, g, prm, out, in, slot0, st, form);

@@ -8,7 +8,9 @@
 // from and appended to a text file ("key<TAB>value" lines) tagged with the
 // device architecture; LQCD_TUNE=0 disables timing (fallback values).
 // The candidates of a kernel compute the same result (each output element is
-// written by one thread with a fixed summation order).
+// written by one thread with a fixed summation order), except that the Schwarz
+// preconditioner in fixed point times its cut launches with the block-resident
+// forms, whose roundings differ.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>

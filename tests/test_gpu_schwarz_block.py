@@ -12,7 +12,10 @@ the two kernels, and a few percent of the FP16 outputs differ by rounding
 steps: there the forms are compared within a tenth of the bound each meets
 against the oracle (the derived bound of the 16-bit preconditioner). The same
 comparison holds for 16-bit fixed point (codes and a per-site norm), whose
-bound is derived beside its own operator tests."""
+bound is derived beside its own operator tests.
+
+(FP16 storage has a block kernel of its own since: its sums run in another order than
+the launches', and its forms 3 and 4 are 1 and 2.)"""
 import numpy as np
 import pytest
 import torch
@@ -121,6 +124,44 @@ def test_fp16_block_kernel_layouts(ctx, monkeypatch, dims, block, recon):
     for f in (1, 2):
         check(outs[f], ref, SCHWARZ_TOL[2], "form %d" % f)
         check(outs[f], outs[0], 0.1 * SCHWARZ_TOL[2], "form %d against the launches" % f)
+
+
+# FP16: x in memory and in registers take the same operations, and which of the
+# launches and the block form runs follows from the sizes alone, so K has the same
+# bits tuned, untuned and with a saved choice of either form. Two 8^4 blocks take the
+# launches; 16 blocks of 4^4 and 64 of 8x8x4x4 the block form. (The two differ in a few
+# percent of the values.)
+@pytest.mark.parametrize("recon", [12, 18])
+@pytest.mark.parametrize("dims,block,form", [((16, 8, 8, 8), (8, 8, 8, 8), 0), ((8, 8, 8, 8), (4, 4, 4, 4), 2),
+                                             ((16, 16, 16, 16), (8, 8, 4, 4), 2)])
+def test_fp16_choice_of_form_is_a_rule(monkeypatch, tmp_path, dims, block, form, recon):
+    U, psi, Ud = Fields.get(dims)
+    src = on_parity(psi, oracle.parity_mask(dims, 0))
+    prm = ops.schwarz_params(block, 4, 0)
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    key = "schwarz p2 r%d %s/%sc m4 c0" % (recon, "x".join(map(str, dims)), "x".join(map(str, block)))
+
+    def run(forced=None, tune=None, saved=None):
+        for v, x in (("LQCD_SCHWARZ_FORM", forced), ("LQCD_TUNE", tune)):
+            monkeypatch.delenv(v, raising=False) if x is None else monkeypatch.setenv(v, x)
+        monkeypatch.delenv("LQCD_TUNE_CACHE", raising=False)
+        if saved is not None:
+            path = tmp_path / ("saved%d" % saved)
+            path.write_text("%s %s\t%d\n" % (arch, key, saved))
+            monkeypatch.setenv("LQCD_TUNE_CACHE", str(path))
+        c = L.lqcd_context_create()
+        o = ops.wilson_clover(c, U, dims, 0.124, 1.0, 2, recon, tile=block, bc_t=-1, U_device=Ud)
+        out = o.spinor()
+        L.lqcd_schwarz_precond(c, o.op, prm, out, o.import_spinor(src, 0))
+        torch.cuda.synchronize()
+        L.lqcd_context_destroy(c)
+        return out
+
+    forms = [run(forced=str(f)) for f in (0, 1, 2)]
+    assert torch.equal(forms[1], forms[2])
+    assert not torch.equal(forms[0], forms[2])
+    for how in ({}, {"tune": "0"}, {"saved": 0}, {"saved": 2}):
+        assert torch.equal(run(**how), forms[form]), how
 
 
 def test_block_form_omega_and_repeat(ctx, monkeypatch):
