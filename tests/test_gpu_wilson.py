@@ -1,4 +1,6 @@
 """GPU parity of the Wilson-clover kernels against the FP64 CPU oracle."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -440,3 +442,33 @@ def test_split_launch_equals_plain(ctx, prec, recon, block, dagger):
                 if p == 0:
                     L.lqcd_schur_apply(ctx, o.op, out, one, dagger, block=block)
                     assert np.array_equal(got[1][j], np_of(o.export_spinor(out, 0)))
+
+
+# The kernels of one thread per site, which take the launches above 16384 points: one
+# source on 18360 sites of a parity, which leaves the last workgroup of 64, 128 or 256
+# threads partly empty, daggered or not, cut or not
+@pytest.mark.parametrize("prec,recon", [(0, 18), (0, 12), (0, 8), (1, 18), (1, 12), (1, 8)])
+@pytest.mark.parametrize("block", [None, (6, 6, 2, 34)])
+@pytest.mark.parametrize("dagger", [0, 1])
+def test_one_thread_kernels_with_a_partial_workgroup(ctx, prec, recon, block, dagger):
+    dims = (18, 6, 10, 34)
+    U, psi, _ = Fields.get(dims)
+    o = make_op(ctx, dims, prec, recon)
+    ref = one_thread_oracle(dims, block, dagger)
+    for p in (0, 1):
+        src = on_parity(psi, oracle.parity_mask(dims, p))
+        inp, out = o.import_spinor(src, p), o.spinor()
+        L.lqcd_dslash(ctx, o.op, out, inp, 1 - p, dagger, block=block)
+        check(np_of(o.export_spinor(out, 1 - p)), ref[p], TOL[prec], "dslash from parity %d" % p)
+        if p == 0:
+            L.lqcd_schur_apply(ctx, o.op, out, inp, dagger, block=block)
+            check(np_of(o.export_spinor(out, 0)), ref[2], TOL[prec], "schur")
+
+
+@functools.lru_cache(maxsize=None)
+def one_thread_oracle(dims, block, dagger):
+    U, psi, _ = Fields.get(dims)
+    ref = oracle.WilsonClover(dims, U, 0.124, 1.0, bc_t=-1)
+    src = [on_parity(psi, oracle.parity_mask(dims, p)) for p in (0, 1)]
+    return [ref.D(src[p], out_parity=1 - p, dagger=bool(dagger), block=block) for p in (0, 1)] + [
+        ref.schur(src[0], dagger=bool(dagger), block=block)]
