@@ -11,8 +11,8 @@ namespace lqcd {
 // Additive Schwarz with each block resident in LDS (Section 4's block solver,
 // with blocks equal to the tiles and 16-bit storage: FP16, BF16, or fixed
 // point with a per-site norm): one workgroup runs every MR step of one block. This
-// form serves BF16 and fixed point, sap_half_kernel below FP16. The block's spinor of the current half step (r on the
-// even sites, then t on the odd sites) lives in LDS, so neighbours are read
+// form serves BF16 and fixed point, sap_half_kernel below FP16. The block's spinor
+// of the current half step (r on the even sites, then t on the odd sites) lives in LDS, so neighbours are read
 // from there; links and clover stream from memory in each half step; the
 // workgroup keeps its sites' r and q (and x, where registers allow) as stored
 // 16-bit values. Per step and even site this moves the links twice and both
@@ -20,8 +20,9 @@ namespace lqcd {
 // the 1152 bytes of two cut Schur launches and an update. The arithmetic is
 // the launches' (same operations, same roundings to the storage format, the
 // same order of the FP64 sums of <q,r> and <q,q>: per 64-site segment by the
-// wave butterfly, then the block's segments in order), so both forms give the
-// same result.
+// wave butterfly, then the block's segments in order): with BF16 both forms give the
+// same result; in fixed point the compiler folds conversions differently in the two,
+// and a few percent of the values differ by rounding steps.
 constexpr int kSapMaxSites = 2048;  // sites per parity of one block (96 KiB of 16-bit spinor)
 
 template <typename S> struct SapArgs {
@@ -462,9 +463,9 @@ __global__ void __launch_bounds__(NT) sap_block_kernel(SapArgs<S> a) {
 // 2170 instead of 3480 vector instructions per pair of sites and MR step. 32^3 x 64,
 // 8^4 blocks, 8 steps: 18 link reals 1323 -> 1103 us, 12 reals 1450 -> 908 us; on
 // 64 CUs alone 0.56 -> 0.36 ms. Bound now by the links and clover words, which do
-// not fit on chip: 7.2 GB (7.7 with x of the second slab) at 7.0 TB/s, where a
-// plain read of as many bytes per CU in a loop reaches 7.5 (8.0 in alternating
-// order). x of both slabs in registers spills (1134 us).
+// not fit on chip: 7.3 GB read and 0.3 written (x of the second slab among them) at
+// 6.7 TB/s, where a plain read of as many bytes per CU in a loop reaches 7.5 (8.0 in
+// alternating order). x of both slabs in registers spills (1134 us).
 constexpr int kSapHalfThreads = 1024;
 constexpr int kNonTemporal = 2;  // of a buffer load
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));

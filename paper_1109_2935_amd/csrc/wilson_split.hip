@@ -273,7 +273,10 @@ __global__ void __launch_bounds__(kSplitThreads) wilson_split_kernel(WArgs<S> a,
 // 19.4 us, 10368 sites 17.6 / 27.7, 16384 sites 19.3 / 26.4, 32768 sites 39.7 /
 // 36.4; FP32 12 reals 2048 sites 11.7 / 12.4, 16384 sites 12.8 / 13.8, 32768
 // sites 18.5 / 17.6. Beyond 16384 points the waves of the one-thread form fill
-// the chip. The 16-bit kernels gained 3-10% and keep the one-thread form: its
+// the chip. Points are counted over the sources: with 2 to 24 sources on 128 to 8192
+// sites, 8, 12 and 18 reals, hop and Schur operator, no launch below the line is
+// slower (1.01 to 1.9 times as fast, the FP32 ones near the line the least), and cut
+// ones gain as much. The 16-bit kernels gained 3-10% and keep the one-thread form: its
 // epilogue rounds some results once where this one would round twice.
 constexpr int64_t kSplitMost = 16384;
 bool wilson_split_fits(const WilsonLaunch &w) {
